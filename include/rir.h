@@ -359,7 +359,7 @@ typedef struct {
  *   poses    host, n_frames * 16 FP64 row-major 4x4 world -> sensor poses
  *            (x_s = R x + t); read before the call returns.
  * FP32 per-voxel arithmetic; the per-block sensor-frame offsets are formed in
- * FP64.  Work is enqueued on `stream` in launches of up to 16 scans; a block
+ * FP64.  Work is enqueued on `stream` in launches of up to 32 scans; a block
  * that no scan of a launch can reach (farther than r_clip + trunc + r0 from
  * every sensor, with both limits set) is not touched.  n_frames = 0 is a
  * no-op.  Errors: RIR_E_INVALID (null, n_frames < 0, non-finite pose,

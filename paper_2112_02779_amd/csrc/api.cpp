@@ -11,6 +11,7 @@
 #include <cstring>
 #include <map>
 #include <memory>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -64,6 +65,19 @@ struct Layout {
 
 // ============================================================================ sensor
 
+// Device memory for the tile maxima of one fusion launch's scans
+// (launch_range_tiles), kept with the sensor: a call takes a slot that its own
+// stream used last or whose last use is over, or makes one (at most
+// kTileSlots; a call that finds none fuses without tile maxima, which gives
+// the same volume).  `done` is recorded after a slot's last launch, and every
+// use waits for it on its stream.
+struct TileSlot {
+    hipStream_t stream = nullptr;
+    hipEvent_t done = nullptr;
+    uint32_t *tiles = nullptr;
+};
+constexpr size_t kTileSlots = 4;
+
 struct rir_sensor {
     uint64_t uid = g_next_uid.fetch_add(1);
     int device = 0;
@@ -75,8 +89,16 @@ struct rir_sensor {
     SensorTab<double> td{};
     const SensorTab<float> *d_tf = nullptr;
     const SensorTab<double> *d_td = nullptr;
+    mutable std::mutex tile_mu;  // held while a call enqueues its launches
+    mutable std::vector<TileSlot> tile_slots;
     ~rir_sensor()
     {
+        if (!tile_slots.empty())
+            hipSetDevice(device);
+        for (auto &t : tile_slots) {
+            hipFree(t.tiles);
+            hipEventDestroy(t.done);
+        }
         if (dmem) {
             hipSetDevice(device);
             hipFree(dmem);
@@ -180,6 +202,9 @@ void fill_tab(SensorTab<T> &tab, const rir_sensor &s, const HostTables &t, char 
     tab.s_hi = std::isfinite(t.s_hi) ? (T)t.s_hi : std::numeric_limits<T>::infinity();
     tab.cos_h = (T)t.cos_h;
     tab.sin_h = (T)t.sin_h;
+    const auto uo = std::minmax_element(t.uoff[0].begin(), t.uoff[0].end());
+    tab.uo_lo = (T)*uo.first;
+    tab.uo_hi = (T)*uo.second;
     tab.row = reinterpret_cast<const T *>(base + *off_row);
     tab.col = reinterpret_cast<const T *>(base + *off_col);
     tab.nrow = reinterpret_cast<const T *>(base + *off_nrow);
@@ -1580,6 +1605,12 @@ static void sdf_common_args(const rir_sensor *sensor, double trunc, double r_cli
     a.cull = (trunc > 0.0 && r_clip > 0.0) ? r_clip + trunc + sensor->r0 + 1e-3 + 1e-4 * (r_clip + trunc) : -1.0;
 }
 
+// Scans one launch takes: their images lie in one buffer descriptor (below 2 GiB).
+static int32_t sdf_launch_frames(int64_t img_bytes)
+{
+    return img_bytes * kSdfFrames < ((int64_t)1 << 31) ? kSdfFrames : kSdfFramesMin;
+}
+
 // World -> sensor poses of k scans (row-major 4x4) as fusion frames.
 static void sdf_frames(const double *poses, int k, SdfFrame *f)
 {
@@ -1591,6 +1622,93 @@ static void sdf_frames(const double *poses, int k, SdfFrame *f)
             f[j].t[r] = T[4 * r + 3];
         }
     }
+}
+
+// Blocks times scans of a launch from which on the tile maxima pay: their
+// launch and the lookups cost about 6 us, which fewer evaluations do not save.
+constexpr int64_t kTileMinWork = 2048;
+
+// A slot for the tile maxima of `per` scans on stream st, or null (see
+// TileSlot; also while st is being captured: a graph would keep the memory).
+// Called with tile_mu held; the capture mode of other streams is left alone
+// (no call here touches memory that a capture could depend on).
+static TileSlot *tile_slot(const rir_sensor *s, int32_t per, hipStream_t st)
+{
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    TileSlot *t = nullptr;
+    for (auto &q : s->tile_slots)
+        if (!t && q.stream == st)
+            t = &q;
+    for (auto &q : s->tile_slots)
+        if (!t && hipEventQuery(q.done) == hipSuccess)
+            t = &q;
+    (void)hipGetLastError();  // "not ready" of a query
+    if (t && hipStreamWaitEvent(st, t->done, 0) != hipSuccess)
+        t = nullptr;
+    if (!t && s->tile_slots.size() < kTileSlots) {
+        TileSlot q;
+        void *mem = nullptr;
+        if (hipMalloc(&mem, range_tiles_count(per, s->H, s->W) * sizeof(uint32_t)) == hipSuccess) {
+            if (hipEventCreateWithFlags(&q.done, hipEventDisableTiming) == hipSuccess) {
+                q.tiles = static_cast<uint32_t *>(mem);
+                s->tile_slots.push_back(q);
+                t = &s->tile_slots.back();
+            } else {
+                hipFree(mem);
+            }
+        }
+        (void)hipGetLastError();
+    }
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (t)
+        t->stream = st;
+    return t;
+}
+
+// Fuses n_frames scans in launches of up to kSdfFrames: the arguments a hold
+// what does not depend on the scans; frame0 is the first scan's index.
+static rir_status sdf_fuse_scans(const rir_sensor *sensor, SdfArgs &a, bool hashed, int32_t n_frames,
+                                 const float *ranges, const double *poses, int64_t frame0, hipStream_t st)
+{
+    const size_t hw = (size_t)sensor->H * sensor->W;
+    const int32_t per = sdf_launch_frames((int64_t)(hw * sizeof(float)));
+    const bool r0 = sensor->r0 > 0.0;
+    const bool pow2 = (sensor->W & (sensor->W - 1)) == 0;
+    const int64_t nblk = hashed ? a.n_blocks : (int64_t)a.nbx * a.nby * a.nbz;
+    std::unique_lock<std::mutex> lock(sensor->tile_mu, std::defer_lock);
+    TileSlot *slot = nullptr;
+    if (nblk * std::min(n_frames, per) >= kTileMinWork) {
+        lock.lock();
+        slot = tile_slot(sensor, per, st);
+    }
+    hipError_t e = hipSuccess;
+    for (int32_t f0 = 0; f0 < n_frames && e == hipSuccess; f0 += per) {
+        const int k = std::min<int32_t>(per, n_frames - f0);
+        a.n_frames = k;
+        a.frame0 = (int)(frame0 + f0);
+        a.ranges = ranges + (size_t)f0 * hw;
+        a.tiles = slot && nblk * k >= kTileMinWork ? slot->tiles : nullptr;
+        sdf_frames(poses + 16 * (size_t)f0, k, a.f);
+        if (a.tiles)
+            e = launch_range_tiles(a.ranges, k, sensor->H, sensor->W, a.clip, slot->tiles, st);
+        if (e == hipSuccess)
+            e = launch_sdf_fuse(a, r0, pow2, hashed, st);
+    }
+    if (slot) {
+        const hipError_t e2 = hipEventRecord(slot->done, st);
+        e = e == hipSuccess ? e2 : e;
+    }
+    HIP_TRY(e);
+    return RIR_OK;
 }
 
 extern "C" rir_status rir_sdf_integrate(const rir_sensor *sensor, const rir_volume_desc *vol, float *voxels,
@@ -1619,7 +1737,7 @@ extern "C" rir_status rir_sdf_integrate(const rir_sensor *sensor, const rir_volu
         if (!std::isfinite(poses[i]))
             return fail(RIR_E_INVALID, "rir_sdf_integrate: non-finite pose");
     const int64_t img_bytes = (int64_t)sensor->H * sensor->W * (int64_t)sizeof(float);
-    if (img_bytes * kSdfFrames >= ((int64_t)1 << 31))
+    if (img_bytes * kSdfFramesMin >= ((int64_t)1 << 31))
         return fail(RIR_E_SHAPE, "rir_sdf_integrate: range images too large for one launch");
     if (n_frames == 0)
         return RIR_OK;
@@ -1634,19 +1752,8 @@ extern "C" rir_status rir_sdf_integrate(const rir_sensor *sensor, const rir_volu
     for (int i = 0; i < 3; ++i)
         a.origin[i] = vol->origin[i];
     a.voxel = vol->voxel;
-    const bool r0 = sensor->r0 > 0.0;
-    const bool pow2 = (sensor->W & (sensor->W - 1)) == 0;
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    for (int32_t f0 = 0; f0 < n_frames; f0 += kSdfFrames) {
-        const int k = std::min<int32_t>(kSdfFrames, n_frames - f0);
-        a.n_frames = k;
-        a.ranges = ranges + (size_t)f0 * (size_t)(img_bytes / (int64_t)sizeof(float));
-        sdf_frames(poses + 16 * (size_t)f0, k, a.f);
-        HIP_TRY(launch_sdf_fuse(a, r0, pow2, false, st));
-    }
-    return RIR_OK;
+    return sdf_fuse_scans(sensor, a, false, n_frames, ranges, poses, 0, static_cast<hipStream_t>(stream));
 }
-
 
 extern "C" rir_status rir_sdf_extract(const rir_volume_desc *vol, const float *voxels, double min_weight,
                                       double max_jump, float *points, int64_t max_points, uint64_t *count,
@@ -1844,7 +1951,7 @@ extern "C" rir_status rir_bvol_integrate(rir_bvol *vol, const rir_sensor *sensor
         if (!std::isfinite(poses[i]))
             return fail(RIR_E_INVALID, "rir_bvol_integrate: non-finite pose");
     const int64_t hw = (int64_t)sensor->H * sensor->W;
-    if (hw * (int64_t)sizeof(float) * kSdfFrames >= ((int64_t)1 << 31))
+    if (hw * (int64_t)sizeof(float) * kSdfFramesMin >= ((int64_t)1 << 31))
         return fail(RIR_E_SHAPE, "rir_bvol_integrate: range images too large for one launch");
     if (vol->n_frames + n_frames > (int64_t)std::numeric_limits<int32_t>::max() / 2)
         return fail(RIR_E_SHAPE, "rir_bvol_integrate: too many scans in the volume's history");
@@ -1852,6 +1959,7 @@ extern "C" rir_status rir_bvol_integrate(rir_bvol *vol, const rir_sensor *sensor
         return RIR_OK;
     HIP_TRY(hipSetDevice(vol->device));
     hipStream_t st = static_cast<hipStream_t>(stream);
+    const int32_t per = sdf_launch_frames(hw * (int64_t)sizeof(float));
     // activation of every scan of the call, each entry keeping its first scan
     BvolActArgs b{};
     b.tab = sensor->d_td;
@@ -1863,8 +1971,8 @@ extern "C" rir_status rir_bvol_integrate(rir_bvol *vol, const rir_sensor *sensor
     b.clip = r_clip;
     b.edge = (double)kSdfEdge * vol->voxel;
     b.t = vol->t;
-    for (int32_t f0 = 0; f0 < n_frames; f0 += kSdfFrames) {
-        const int k = std::min<int32_t>(kSdfFrames, n_frames - f0);
+    for (int32_t f0 = 0; f0 < n_frames; f0 += per) {
+        const int k = std::min<int32_t>(per, n_frames - f0);
         b.n_frames = k;
         b.frame0 = (int)(vol->n_frames + f0);
         b.ranges = ranges + (size_t)f0 * (size_t)hw;
@@ -1890,16 +1998,9 @@ extern "C" rir_status rir_bvol_integrate(rir_bvol *vol, const rir_sensor *sensor
     a.blocks = vol->t.blocks;
     a.act = vol->t.act;
     a.n_blocks = (int)vol->n_blocks;
-    const bool r0 = sensor->r0 > 0.0;
-    const bool pow2 = (sensor->W & (sensor->W - 1)) == 0;
-    for (int32_t f0 = 0; f0 < n_frames; f0 += kSdfFrames) {
-        const int k = std::min<int32_t>(kSdfFrames, n_frames - f0);
-        a.n_frames = k;
-        a.frame0 = (int)(vol->n_frames + f0);
-        a.ranges = ranges + (size_t)f0 * (size_t)hw;
-        sdf_frames(poses + 16 * (size_t)f0, k, a.f);
-        HIP_TRY(launch_sdf_fuse(a, r0, pow2, true, st));
-    }
+    const rir_status s = sdf_fuse_scans(sensor, a, true, n_frames, ranges, poses, vol->n_frames, st);
+    if (s != RIR_OK)
+        return s;
     vol->n_frames += n_frames;
     return RIR_OK;
 }

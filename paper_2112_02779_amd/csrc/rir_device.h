@@ -35,6 +35,7 @@ struct SensorTab {
     int nbins[kMaxLevels];
     T r0, s_lo, s_hi, cos_h, sin_h;
     T bin_lo[kMaxLevels], bin_scale[kMaxLevels], kW[kMaxLevels];
+    T uo_lo, uo_hi;  // smallest and largest column offset of the finest level
     const T *row, *col, *nrow, *theta;
     const T *ebin[kMaxLevels];
 };
@@ -106,6 +107,12 @@ __device__ __forceinline__ rsrc_t make_rsrc(const void *p, uint32_t bytes)
 __device__ __forceinline__ uint32_t bld_u32(rsrc_t r, uint32_t off)
 {
     return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
+}
+
+// The same with a wave-uniform part of the offset in a scalar register.
+__device__ __forceinline__ uint32_t bld_u32s(rsrc_t r, uint32_t off, uint32_t uni)
+{
+    return __builtin_amdgcn_raw_buffer_load_b32(r, off, uni, 0);
 }
 
 template <typename T>

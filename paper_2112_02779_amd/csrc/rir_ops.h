@@ -9,7 +9,10 @@
 namespace rir {
 
 constexpr int kSdfEdge = 16;     // voxels per block edge
-constexpr int kSdfFrames = 16;   // scans per launch (their poses travel as kernel arguments)
+// Scans per launch (their poses travel as kernel arguments, 3 KB of the 4 KB
+// a launch takes), and the number that always fits one launch's 2 GiB of
+// images (the entry points refuse scans 16 of which do not).
+constexpr int kSdfFrames = 32, kSdfFramesMin = 16;
 
 // World -> sensor pose of one scan (Eq. (8)): x_s = R x + t, R row-major.
 struct SdfFrame {
@@ -40,7 +43,22 @@ struct SdfArgs {
     const int *act;
     int n_blocks;
     int frame0;
+    const uint32_t *tiles;  // tile maxima of the launch's scans (launch_range_tiles), or null
 };
+
+// Tile maxima of scans: tiles of 1 row x kTileCols columns, and of kTileMerge x
+// kTileMerge of those.
+constexpr int kTileCols = 16, kTileMerge = 4;
+inline size_t range_tiles_count(int n_frames, int H, int W)
+{
+    return (size_t)n_frames * ((size_t)H * ((W + kTileCols - 1) / kTileCols) +
+                               (size_t)((H + kTileMerge - 1) / kTileMerge) *
+                                   ((W + kTileCols * kTileMerge - 1) / (kTileCols * kTileMerge)));
+}
+hipError_t launch_range_tiles(const float *ranges, int n_frames, int H, int W, float clip, uint32_t *tiles,
+                              hipStream_t stream);
+
+static_assert(sizeof(SdfArgs) <= 4096, "kernel arguments");
 
 // One fusion launch over every block of the grid (hashed: of the pool).
 hipError_t launch_sdf_fuse(const SdfArgs &a, bool r0, bool pow2, bool hashed, hipStream_t stream);

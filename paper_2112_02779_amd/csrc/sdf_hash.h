@@ -43,6 +43,8 @@ struct BvolActArgs {
     BvolDev t;
 };
 
+static_assert(sizeof(BvolActArgs) <= 4096, "kernel arguments");
+
 hipError_t launch_bvol_activate(const BvolActArgs &a, hipStream_t stream);
 hipError_t launch_bvol_neighbors(const BvolDev &t, int n_blocks, int *nbr, hipStream_t stream);
 hipError_t launch_bvol_export(const BvolDev &t, int n_blocks, int4 *out, hipStream_t stream);
