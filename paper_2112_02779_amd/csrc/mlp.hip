@@ -41,12 +41,7 @@ __global__ __launch_bounds__(256) void k_mlp_forward(MlpDev m, const float *feat
 __device__ __forceinline__ bf16x4_t lds_bf4(const uint16_t *p)
 {
     const uint2 v = *reinterpret_cast<const uint2 *>(p);
-    bf16x4_t b;
-    b[0] = (short)(v.x & 0xffffu);
-    b[1] = (short)(v.x >> 16);
-    b[2] = (short)(v.y & 0xffffu);
-    b[3] = (short)(v.y >> 16);
-    return b;
+    return bf4(v.x, v.y);
 }
 
 __device__ __forceinline__ void wave_lds_sync()
@@ -56,100 +51,140 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Gradient of the summed loss over this wavefront's samples.  Record layout:
-// W1[64][14], b1[64], W2[64][64], b2[64], W3[64], b3, loss.
-__global__ __launch_bounds__(256) void k_mlp_grad(MlpDev m, const float *feats, const float *labels, int64_t B,
-                                                  float *gpart)
+// Sum over the 16 lanes of a DPP row (every lane gets it).
+__device__ __forceinline__ float row_sum16(float v)
 {
-    __shared__ uint32_t s_feat[kMlpGradWaves][64 * 8];    // [pixel][16 bf16]
-    __shared__ uint16_t s_g2[kMlpGradWaves][64 * 16];     // [h2][px of the tile]
-    __shared__ uint16_t s_h1[kMlpGradWaves][64 * 16];     // [h1][px]
-    __shared__ uint16_t s_g1[kMlpGradWaves][64 * 16];     // [h1][px]
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xf, 0xf, false));
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x124, 0xf, 0xf, false));
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x122, 0xf, 0xf, false));
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x121, 0xf, 0xf, false));
+    return v;
+}
+
+// Gradient of the summed loss over this wavefront's samples: `per` (16, 32 or
+// 64) at a time.  Record layout: W1[64][14], b1[64], W2[64][64], b2[64],
+// W3[64], b3, loss.
+//
+// Bound by latency: the matrix products of a training batch of 8192 take well
+// under a microsecond of the chip, so the batch is cut into as many
+// wavefronts as the record limit allows (mlp_grad_per) and each one's chain
+// is kept short: W2 goes through shared memory once per workgroup (its
+// transposed fragments are 64 two-byte reads a lane, slow from memory), the
+// other fragments are 8- and 16-byte loads, each lane loads its own
+// operand's features, and row sums are DPP rotations.  Batch of 8192 on an
+// MI355X: 31 -> 14.6 us (64 samples a wavefront, two-byte weight loads before).
+__global__ __launch_bounds__(256) void k_mlp_grad(MlpDev m, const float *feats, const float *labels, int64_t B,
+                                                  int per, float *gpart)
+{
+    __shared__ __align__(16) uint16_t s_w2[64 * 64];                    // [h2][h1]
+    __shared__ __align__(16) uint16_t s_f[kMlpGradWaves][16 * 16];      // [sample][input]
+    __shared__ __align__(16) uint16_t s_g2[kMlpGradWaves][64 * 16];     // [h2][sample]
+    __shared__ __align__(16) uint16_t s_h1[kMlpGradWaves][64 * 16];     // [h1][sample]
+    __shared__ __align__(16) uint16_t s_g1[kMlpGradWaves][64 * 16];     // [h1][sample]
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, g = lane >> 4;
-    MlpFrag F;
-    mlp_load(m, F);
-    // W2^T fragments: rows h1 = mt*16 + r, inputs h2 = kt*16 + 4g + j
-    bf16x4_t a2t[4][4];
+    const int64_t stride = (int64_t)gridDim.x * kMlpGradWaves * per;
+    const int64_t base0 = ((int64_t)blockIdx.x * kMlpGradWaves + wave) * per;
+    // features 4 g .. 4 g + 3 of sample s (two zero inputs make 16) and its label
+    auto load_sample = [&](int64_t s, float (&f)[4], float &y) {
+        const bool ok = s < B;
+        const float *p = feats + 14 * s + 4 * g;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            f[j] = ok && (j < 2 || g < 3) ? p[j] : 0.f;
+        y = ok ? labels[s] : 0.f;
+    };
+    float fx[4], yx;
+    load_sample(base0 + r, fx, yx);
+    {
+        const uint4 *src = reinterpret_cast<const uint4 *>(m.w + kMlpW2);
+        uint4 *dst = reinterpret_cast<uint4 *>(s_w2);
+        dst[threadIdx.x] = src[threadIdx.x];
+        dst[threadIdx.x + 256] = src[threadIdx.x + 256];
+    }
+    bf16x4_t a1[4], a2[4][4], a2t[4][4];
+    f32x4_t b1v[4], b2v[4];
+    float w3[4][4];
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+        // W1 rows mt * 16 + r, inputs 4 g ..: 28-byte rows, so 4-byte loads
+        const uint32_t *p1 = reinterpret_cast<const uint32_t *>(m.w + kMlpW1 + (mt * 16 + r) * 14 + 4 * g);
+        const uint2 p3 = *reinterpret_cast<const uint2 *>(m.w + kMlpW3 + mt * 16 + 4 * g);
+        a1[mt] = bf4(p1[0], g < 3 ? p1[1] : 0u);
+        b1v[mt] = *reinterpret_cast<const f32x4_t *>(m.b + kMlpB1 + mt * 16 + 4 * g);
+        b2v[mt] = *reinterpret_cast<const f32x4_t *>(m.b + kMlpB2 + mt * 16 + 4 * g);
+        w3[mt][0] = bf2f(p3.x & 0xffffu);
+        w3[mt][1] = bf2f(p3.x >> 16);
+        w3[mt][2] = bf2f(p3.y & 0xffffu);
+        w3[mt][3] = bf2f(p3.y >> 16);
+    }
+    const float b3 = m.b[kMlpB3];
+    __syncthreads();
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
-        for (int kt = 0; kt < 4; ++kt)
+        for (int kt = 0; kt < 4; ++kt) {
+            a2[mt][kt] = lds_bf4(s_w2 + (mt * 16 + r) * 64 + kt * 16 + 4 * g);
+            // W2^T: rows h1 = mt * 16 + r, inputs h2 = kt * 16 + 4 g + j
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                a2t[mt][kt][j] = (short)m.w[kMlpW2 + (kt * 16 + 4 * g + j) * 64 + mt * 16 + r];
+                a2t[mt][kt][j] = (short)s_w2[(kt * 16 + 4 * g + j) * 64 + mt * 16 + r];
+        }
     f32x4_t dW2[4][4], dW1[4];
+    float dW3[4][4], db2[4][4], db1[4][4];
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
         dW1[a] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
+        for (int b = 0; b < 4; ++b) {
             dW2[a][b] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+            dW3[a][b] = db2[a][b] = db1[a][b] = 0.f;
+        }
     }
-    float dW3[4][4], db2[4][4], db1[4][4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            dW3[a][j] = db2[a][j] = db1[a][j] = 0.f;
     float db3 = 0.f, loss = 0.f;
     const float invB = 1.f / (float)B;
-    uint32_t *sf = s_feat[wave];
-    uint16_t *sfh = reinterpret_cast<uint16_t *>(sf);
-    uint16_t *sg2 = s_g2[wave], *sh1 = s_h1[wave], *sg1 = s_g1[wave];
-    const int64_t stride = (int64_t)gridDim.x * kMlpGradWaves * 64;
-    for (int64_t base = ((int64_t)blockIdx.x * kMlpGradWaves + wave) * 64; base < B; base += stride) {
-        {
-            const int64_t i = base + lane;
-            float f[14];
-#pragma unroll
-            for (int k = 0; k < 14; ++k)
-                f[k] = i < B ? feats[14 * i + k] : 0.f;
-            uint32_t fp[8];
-            pack_features(f, fp);
-            uint4 *row = reinterpret_cast<uint4 *>(sf + lane * 8);
-            row[0] = make_uint4(fp[0], fp[1], fp[2], fp[3]);
-            row[1] = make_uint4(fp[4], fp[5], fp[6], fp[7]);
-        }
-        wave_lds_sync();
+    uint16_t *sf = s_f[wave], *sg2 = s_g2[wave], *sh1 = s_h1[wave], *sg1 = s_g1[wave];
+    for (int64_t base = base0; base < B; base += stride) {
 #pragma unroll 1
-        for (int nt = 0; nt < 4; ++nt) {
-            const int64_t smp = base + nt * 16 + r;  // sample of this lane's column
+        for (int t = 0; t < per; t += 16) {
+            const int64_t smp = base + t + r;  // sample of this lane's column
             const bool ok = smp < B;
+            const float y = yx;
+            const uint32_t f01 = pack_bf2(fx[0], fx[1]), f23 = pack_bf2(fx[2], fx[3]);
+            const bf16x4_t Bf = bf4(f01, f23);
+            *reinterpret_cast<uint2 *>(sf + r * 16 + 4 * g) = make_uint2(f01, f23);
+            // the next tile's sample
+            load_sample(t + 16 < per ? smp + 16 : base + stride + r, fx, yx);
             // ---- forward
-            const bf16x4_t Bf = lds_bf4(sfh + (nt * 16 + r) * 16 + 4 * g);
             bf16x4_t hb[4];
             bool m1[4][4];
 #pragma unroll
             for (int mt = 0; mt < 4; ++mt) {
-                f32x4_t c = {F.b1[mt][0], F.b1[mt][1], F.b1[mt][2], F.b1[mt][3]};
-                c = mfma16(F.a1[mt], Bf, c);
+                const f32x4_t c = mfma16(a1[mt], Bf, b1v[mt]);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
+                for (int j = 0; j < 4; ++j)
                     m1[mt][j] = c[j] > 0.f;
-                    hb[mt][j] = (short)f2bf(fmaxf(c[j], 0.f));
-                }
+                hb[mt] = bf4(pack_bf2(fmaxf(c[0], 0.f), fmaxf(c[1], 0.f)), pack_bf2(fmaxf(c[2], 0.f), fmaxf(c[3], 0.f)));
             }
             float h2[4][4];
             bool m2[4][4];
             float part = 0.f;
 #pragma unroll
             for (int mt = 0; mt < 4; ++mt) {
-                f32x4_t c = {F.b2[mt][0], F.b2[mt][1], F.b2[mt][2], F.b2[mt][3]};
+                f32x4_t c = b2v[mt];
 #pragma unroll
                 for (int kt = 0; kt < 4; ++kt)
-                    c = mfma16(F.a2[mt][kt], hb[kt], c);
+                    c = mfma16(a2[mt][kt], hb[kt], c);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     m2[mt][j] = c[j] > 0.f;
                     h2[mt][j] = round_bf(fmaxf(c[j], 0.f));
-                    part += F.w3[mt][j] * h2[mt][j];
+                    part += w3[mt][j] * h2[mt][j];
                 }
             }
             part += __shfl_xor(part, 16, 64);
             part += __shfl_xor(part, 32, 64);
-            const float z = part + F.b3;
+            const float z = part + b3;
             // ---- loss and output delta
-            const float y = ok ? labels[smp] : 0.f;
             const float sp = z > 0.f ? z + log1pf(__expf(-z)) : log1pf(__expf(z));
             if (ok && g == 0)
                 loss += sp - y * z;
@@ -163,10 +198,10 @@ __global__ __launch_bounds__(256) void k_mlp_grad(MlpDev m, const float *feats, 
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     dW3[mt][j] += dz * h2[mt][j];
-                    const float d2 = round_bf(m2[mt][j] ? F.w3[mt][j] * dz : 0.f);
-                    db2[mt][j] += d2;
-                    g2b[mt][j] = (short)f2bf(d2);
-                    sg2[(mt * 16 + 4 * g + j) * 16 + r] = (uint16_t)f2bf(d2);
+                    const uint32_t d2 = f2bf(m2[mt][j] ? w3[mt][j] * dz : 0.f);
+                    db2[mt][j] += bf2f(d2);
+                    g2b[mt][j] = (short)d2;
+                    sg2[(mt * 16 + 4 * g + j) * 16 + r] = (uint16_t)d2;
                     sh1[(mt * 16 + 4 * g + j) * 16 + r] = (uint16_t)hb[mt][j];
                 }
             // ---- hidden-1 deltas: W2^T g2
@@ -178,24 +213,27 @@ __global__ __launch_bounds__(256) void k_mlp_grad(MlpDev m, const float *feats, 
                     c = mfma16(a2t[mt][kt], g2b[kt], c);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const float d1 = round_bf(m1[mt][j] ? c[j] : 0.f);
-                    db1[mt][j] += d1;
-                    sg1[(mt * 16 + 4 * g + j) * 16 + r] = (uint16_t)f2bf(d1);
+                    const uint32_t d1 = f2bf(m1[mt][j] ? c[j] : 0.f);
+                    db1[mt][j] += bf2f(d1);
+                    sg1[(mt * 16 + 4 * g + j) * 16 + r] = (uint16_t)d1;
                 }
             }
             wave_lds_sync();
             // ---- weight gradients, contracting over the 16 samples of the tile
+            bf16x4_t Bx, H1[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                Bx[j] = (short)sf[(4 * g + j) * 16 + r];
+#pragma unroll
+            for (int n = 0; n < 4; ++n)
+                H1[n] = lds_bf4(sh1 + (n * 16 + r) * 16 + 4 * g);
 #pragma unroll
             for (int mt = 0; mt < 4; ++mt) {
                 const bf16x4_t A2 = lds_bf4(sg2 + (mt * 16 + r) * 16 + 4 * g);
 #pragma unroll
                 for (int n = 0; n < 4; ++n)
-                    dW2[mt][n] = mfma16(A2, lds_bf4(sh1 + (n * 16 + r) * 16 + 4 * g), dW2[mt][n]);
+                    dW2[mt][n] = mfma16(A2, H1[n], dW2[mt][n]);
                 const bf16x4_t A1 = lds_bf4(sg1 + (mt * 16 + r) * 16 + 4 * g);
-                bf16x4_t Bx;
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    Bx[j] = (short)sfh[(nt * 16 + 4 * g + j) * 16 + r];
                 dW1[mt] = mfma16(A1, Bx, dW1[mt]);
             }
             wave_lds_sync();
@@ -213,24 +251,16 @@ __global__ __launch_bounds__(256) void k_mlp_grad(MlpDev m, const float *feats, 
                 rec[960 + h * 64 + n * 16 + r] = dW2[mt][n][j];
             if (r < 14)
                 rec[h * 14 + r] = dW1[mt][j];
-            float a = dW3[mt][j], b2 = db2[mt][j], b1 = db1[mt][j];
-#pragma unroll
-            for (int s = 1; s < 16; s <<= 1) {
-                a += __shfl_xor(a, s, 64);
-                b2 += __shfl_xor(b2, s, 64);
-                b1 += __shfl_xor(b1, s, 64);
-            }
+            const float a = row_sum16(dW3[mt][j]), b2 = row_sum16(db2[mt][j]), b1 = row_sum16(db1[mt][j]);
             if (r == 0) {
                 rec[5120 + h] = a;
                 rec[5056 + h] = b2;
                 rec[896 + h] = b1;
             }
         }
-#pragma unroll
-    for (int s = 1; s < 64; s <<= 1) {
-        db3 += __shfl_xor(db3, s, 64);
-        loss += __shfl_xor(loss, s, 64);
-    }
+    // lanes 0..15 hold the sums over samples of b3 and the loss (g = 0)
+    db3 = row_sum16(db3);
+    loss = row_sum16(loss);
     if (lane == 0) {
         rec[5184] = db3;
         rec[5185] = loss;
@@ -240,22 +270,52 @@ __global__ __launch_bounds__(256) void k_mlp_grad(MlpDev m, const float *feats, 
 // Sums the gradient records in a fixed order (FP64) and applies one Adam step
 // (beta1 0.9, beta2 0.999, eps 1e-8, bias-corrected) to the FP32 master
 // weights and the biases; the bf16 weights are re-rounded from the masters.
-__global__ __launch_bounds__(256) void k_mlp_adam(const float *gpart, int nrec, int64_t B, float lr, int step,
-                                                  float *master, float *bias, float *m1, float *m2, uint16_t *wbf,
-                                                  float *loss_out, float *grads_out)
+// Bound by the one read of the records (a batch of 8192: 512 records, 10.6
+// MB): a workgroup takes 64 parameters, its 16 wavefronts every 16th record
+// each (all those loads in flight together), and adds their sums in wavefront
+// order.  One thread per parameter walking all records one after the other
+// took 40 us for 128 records; now 4.8 us for 512.
+constexpr int kAdamParams = 64, kAdamGroups = 16;
+
+__global__ __launch_bounds__(kAdamParams *kAdamGroups) void k_mlp_adam(const float *gpart, int nrec, int64_t B,
+                                                                       float lr, int step, float *master, float *bias,
+                                                                       float *m1, float *m2, uint16_t *wbf,
+                                                                       float *loss_out, float *grads_out)
 {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j == 5185 && loss_out) {
+    __shared__ double s_sum[kAdamGroups][kAdamParams];
+    const int p = threadIdx.x & (kAdamParams - 1), grp = threadIdx.x / kAdamParams;
+    const int j = blockIdx.x * kAdamParams + p;
+    {
         double s = 0.0;
-        for (int k = 0; k < nrec; ++k)
-            s += (double)gpart[(size_t)k * kMlpGradRecord + 5185];
-        loss_out[0] = (float)(s / (double)B);
+        if (j < kMlpGradRecord) {
+            const float *q = gpart + j;
+            int k = grp;
+            for (; k + 7 * kAdamGroups < nrec; k += 8 * kAdamGroups) {
+                float v[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    v[i] = q[(size_t)(k + i * kAdamGroups) * kMlpGradRecord];
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    s += (double)v[i];
+            }
+            for (; k < nrec; k += kAdamGroups)
+                s += (double)q[(size_t)k * kMlpGradRecord];
+        }
+        s_sum[grp][p] = s;
     }
-    if (j >= 5185)
+    __syncthreads();
+    if (grp != 0 || j >= kMlpGradRecord)
         return;
     double s = 0.0;
-    for (int k = 0; k < nrec; ++k)
-        s += (double)gpart[(size_t)k * kMlpGradRecord + j];
+#pragma unroll
+    for (int w = 0; w < kAdamGroups; ++w)
+        s += s_sum[w][p];
+    if (j == 5185) {
+        if (loss_out)
+            loss_out[0] = (float)(s / (double)B);
+        return;
+    }
     const float gj = (float)s;
     if (grads_out)
         grads_out[j] = gj;
@@ -315,9 +375,14 @@ hipError_t mlp_scratch(int device, float **out)
     return hipSuccess;
 }
 
+// Samples a wavefront of the gradient kernel takes at a time: the fewest that
+// keep a batch within 512 records (the allocation-free step's array; a record
+// costs 20.7 KB of writes and reads), else 64.
+static int mlp_grad_per(int64_t B) { return B <= 512 * 16 ? 16 : (B <= 512 * 32 ? 32 : 64); }
+
 int mlp_grad_blocks(int64_t B)
 {
-    int64_t nb = (B + 64 * kMlpGradWaves - 1) / (64 * kMlpGradWaves);
+    const int64_t per = (int64_t)mlp_grad_per(B) * kMlpGradWaves, nb = (B + per - 1) / per;
     return (int)(nb < 1 ? 1 : (nb > 512 ? 512 : nb)) * kMlpGradWaves;
 }
 
@@ -333,14 +398,15 @@ hipError_t launch_mlp_grad(const MlpDev &m, const float *feats, const float *lab
                            int nrec, hipStream_t stream)
 {
     hipLaunchKernelGGL(k_mlp_grad, dim3(nrec / kMlpGradWaves), dim3(64 * kMlpGradWaves), 0, stream, m, feats, labels,
-                       B, gpart);
+                       B, mlp_grad_per(B), gpart);
     return hipGetLastError();
 }
 
 hipError_t launch_mlp_adam(const float *gpart, int nrec, int64_t B, float lr, int step, float *master, float *bias,
                            float *m1, float *m2, uint16_t *wbf, float *loss_out, float *grads_out, hipStream_t stream)
 {
-    hipLaunchKernelGGL(k_mlp_adam, dim3((5186 + 255) / 256), dim3(256), 0, stream, gpart, nrec, B, lr, step, master,
+    hipLaunchKernelGGL(k_mlp_adam, dim3((kMlpGradRecord + kAdamParams - 1) / kAdamParams),
+                       dim3(kAdamParams * kAdamGroups), 0, stream, gpart, nrec, B, lr, step, master,
                        bias, m1, m2, wbf, loss_out, grads_out);
     return hipGetLastError();
 }

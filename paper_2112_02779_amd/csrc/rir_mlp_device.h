@@ -79,41 +79,9 @@ __device__ __forceinline__ f32x4_t mfma16(bf16x4_t a, bf16x4_t b, f32x4_t c)
     return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
 }
 
-// Per-lane operand fragments of the network (lane l: r = l % 16, g = l / 16).
-//  a1[mt]      W1 rows mt*16 + r, inputs 4g..4g+3 (inputs >= 14 are zero)
-//  a2[mt][kt]  W2 rows mt*16 + r, inputs kt*16 + 4g..+3
-//  b1, b2, w3  [mt][j] for hidden unit mt*16 + 4g + j
-struct MlpFrag {
-    bf16x4_t a1[4];
-    bf16x4_t a2[4][4];
-    float b1[4][4], b2[4][4], w3[4][4];
-    float b3;
-};
-
-__device__ __forceinline__ void mlp_load(const MlpDev &m, MlpFrag &F)
-{
-    const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int k = 4 * g + j;
-            F.a1[mt][j] = (short)(k < 14 ? m.w[kMlpW1 + (mt * 16 + r) * 14 + k] : 0);
-            F.b1[mt][j] = m.b[kMlpB1 + mt * 16 + k];
-            F.b2[mt][j] = m.b[kMlpB2 + mt * 16 + k];
-            F.w3[mt][j] = bf2f(m.w[kMlpW3 + mt * 16 + k]);
-        }
-#pragma unroll
-        for (int kt = 0; kt < 4; ++kt)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                F.a2[mt][kt][j] = (short)m.w[kMlpW2 + (mt * 16 + r) * 64 + kt * 16 + 4 * g + j];
-    }
-    F.b3 = m.b[kMlpB3];
-}
-
 // Inference fragments (lane l: r = l % 16, g = l / 16).  Layer 1 uses K = 16
-// products (a1, b1 as in MlpFrag).  Layers 2 and 3 use K = 32 products whose
+// products: a1[mt] holds W1 row mt * 16 + r, inputs 4 g .. 4 g + 3 (zero past
+// 13), b1 and b2 [mt][j] the bias of unit mt * 16 + 4 g + j.  Layers 2 and 3 use K = 32 products whose
 // chunk c covers hidden units 32 c .. 32 c + 31 in the order that makes a
 // chunk of B the two K = 16 output tiles 2c and 2c + 1 of the lane itself:
 // operand index 8 g + j is unit (2 c + j / 4) * 16 + 4 g + j % 4.  a2[mt][c]
