@@ -1010,6 +1010,21 @@ bool learned_at(const rir_icp_params *p, int level)
     return p->weight_mode == RIR_WEIGHT_LEARNED && (p->learned_levels == 0 || ((p->learned_levels >> level) & 1));
 }
 
+// Row segments each wavefront of a step launch keeps in flight: never more
+// than it has in a tile.  A coarse level's tile holds 2 (or 1) per wavefront,
+// and the empty places of a chunk of 4 are computed all the same (level 2 of
+// 99 pairs of 128x2048: 23.3 us an iteration with 4, 21.2 with 2; of 24 pairs
+// of 64x1000 in the general form: 15.1 and 12.0).  The order of the sums,
+// hence the result, does not depend on it.
+int step_chunk(const Plan *P, int level)
+{
+    const int per_wave = std::max(1, P->tile_seg[level] / (P->block / kSegPx));
+    int c = P->key.k.tune.chunk;
+    while (c > per_wave)
+        c >>= 1;
+    return c;
+}
+
 // Arguments of the launches of one iteration; lane >= 0 restricts them to
 // that sub-batch's pairs and tiles.
 StepArgs step_args(const Plan *P, const rir_icp_params *p, int level, int iter, int mode, int lane = -1)
@@ -1028,7 +1043,7 @@ StepArgs step_args(const Plan *P, const rir_icp_params *p, int level, int iter, 
     a.iter = iter;
     a.levels = P->key.k.levels;
     a.tile_seg = P->tile_seg[level];
-    a.chunk = P->key.k.tune.chunk;
+    a.chunk = step_chunk(P, level);
     a.xcd_remap = P->key.k.tune.xcd_remap;
     a.mode = mode;
     a.iters = P->key.k.iters[level];
@@ -1107,8 +1122,11 @@ rir_status enqueue_level(const Plan *P, const rir_icp_params *p, int l, hipStrea
 {
     const int np = lane < 0 ? P->n_pairs : P->lane_p0[lane + 1] - P->lane_p0[lane];
     const int grid = lane < 0 ? P->grid[l] : P->lane_grid[l][lane];
-    if (P->resident[l] && P->key.k.iters[l] > 0)
-        HIP_TRY(launch_level(P->fp64, step_args(P, p, l, 0, kStepNormal, lane), np, st));
+    if (P->resident[l] && P->key.k.iters[l] > 0) {
+        StepArgs r = step_args(P, p, l, 0, kStepNormal, lane);
+        r.chunk = P->key.k.tune.chunk;  // the whole level image, not a tile
+        HIP_TRY(launch_level(P->fp64, r, np, st));
+    }
     if (step_args(P, p, l, 0, kStepNormal, lane).n_tiles == 0)
         return RIR_OK;
     for (int it = 0; it < P->key.k.iters[l]; ++it) {

@@ -338,34 +338,27 @@ __global__ __launch_bounds__(256) void k_nbr_feats(NbrArgs a)
 
 // ----------------------------------------------------------------------------- solve
 
-// FP64 lane exchange helpers for the wavefront solve.
-__device__ __forceinline__ double rlane(double v, int src)
-{
-    const uint64_t b = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, src);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), src);
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-__device__ __forceinline__ double shfl_d(double v, int src) { return __shfl(v, src, 64); }
-
 // Start of row r of the packed upper triangle of a symmetric 6x6 matrix
 // (21 entries, row-major): entry (r, c), c >= r, is tri_off(r) + c - r.
-__device__ __forceinline__ int tri_off(int r) { return r * 6 - (r * (r - 1)) / 2; }
+__device__ __forceinline__ constexpr int tri_off(int r) { return r * 6 - (r * (r - 1)) / 2; }
 
-// The Gauss-Newton update of one pair (Eq. (7)) by one wavefront, each lane
-// holding one entry, so that the solve needs few registers and no single
-// lane walks the whole factorisation:
-//  - lane t < 21 holds entry t of the packed J^T W J; the upper Cholesky
-//    factor U (U^T U = J^T W J) is formed in place, right-looking: at step j
-//    row j is finished (pivot sqrt, row scaled by its reciprocal) and every
-//    later entry (r, c) subtracts U(j, r) U(j, c), so each entry sees its
+// The Gauss-Newton update of one pair (Eq. (7)) by one wavefront.  It is the
+// serial tail of every iteration (the next one waits for it), bound by the
+// latency of its FP64 chain, so no value crosses lanes inside the
+// factorisation:
+//  - every lane holds the whole packed J^T W J and forms the upper Cholesky
+//    factor U (U^T U = J^T W J) in place, right-looking: at step j row j is
+//    finished (pivot sqrt, row scaled by its reciprocal) and every later
+//    entry (r, c) subtracts U(j, r) U(j, c), so each entry sees its
 //    subtractions in ascending j as in the textbook left-looking form.  A
 //    pivot not above 1e-12 times the largest diagonal entry fails;
-//  - lanes 0..5 solve U^T y = -g, then U xi = y;
+//  - every lane solves U^T y = -g, then U xi = y;
 //  - lanes 0..11 form T <- Exp(xi) T (left update, Exp(xi) = [R, V tau] with
 //    R = I + A K + B K^2, V = I + B K + C K^2, K = [omega]x, A = sin a / a,
 //    B = (1 - cos a) / a^2, C = (a - sin a) / a^3, Taylor below a = 1e-6),
 //    one pose entry each.
+// One entry per lane, exchanged by lane permutes (about 130 cycles each, 24 of
+// them in a row), gave the same poses in 7000-8100 cycles, this takes 4300-5000.
 // Then the per-level statistics.  tot: the 30 FP64 sums (J^T W J, J^T W e,
 // sum w, sum w e^2, robust cost), cnt: valid, inlier and projection counts.
 // Called by all 64 lanes of one wavefront; returns (wave-uniform) whether the
@@ -379,72 +372,54 @@ __device__ __forceinline__ bool solve_pair_wave(const StepArgs &a, int pair, int
     // pixel loop
     asm volatile("" : "+v"(lane));
     const int l = a.level;
-    const bool isU = lane < 21;
-    int ur = 0, uc = 0;  // (row, column) of this lane's entry
-    {
-        int t = lane;
-#pragma unroll
-        for (int r = 0; r < 6; ++r) {
-            const int len = 6 - r;
-            if (t >= 0 && t < len) {
-                ur = r;
-                uc = r + t;
-            }
-            t -= len;
-        }
-    }
     const double tv = lane < 30 ? tot[lane] : 0.0;
     const double sum_w = tot[27], sum_we2 = tot[28], rho = tot[29];
     const int n_valid = (int)cnt[0];
     const bool finite = __builtin_amdgcn_ballot_w64(lane < 30 && !isfinite(tv)) == 0;
     rir_level_stats *out = a.stats + (a.mode == kStepDebug ? 0 : (size_t)pair * a.levels + l);
-    if (isU)
+    if (lane < 21)
         out->JtJ[lane] = tv;
-    double U = isU ? tv : 0.0;
+    double U[21], v[6];  // v: -g, then y, then xi
+#pragma unroll
+    for (int t = 0; t < 21; ++t)
+        U[t] = tot[t];
+#pragma unroll
+    for (int t = 0; t < 6; ++t)
+        v[t] = -tot[21 + t];
     double dmax = 0.0;
 #pragma unroll
-    for (int j = 0; j < 6; ++j) {
-        const double d = rlane(U, tri_off(j));
-        dmax = d > dmax ? d : dmax;
-    }
+    for (int j = 0; j < 6; ++j)
+        dmax = U[tri_off(j)] > dmax ? U[tri_off(j)] : dmax;
     bool ok = n_valid >= 6 && finite && dmax > 0.0;
-    double rinv = 0.0, v = 0.0;  // lane j < 6: 1 / U(j, j); then y_j, then xi_j
     if (ok) {
+        double rinv[6];  // 1 / U(j, j)
 #pragma unroll
         for (int j = 0; j < 6; ++j) {
-            const double d = rlane(U, tri_off(j));
+            const double d = U[tri_off(j)];
             ok = ok && d > 1e-12 * dmax;
             const double sd = sqrt(d > 0.0 ? d : 1.0), inv = 1.0 / sd;
-            if (lane == j)
-                rinv = inv;
-            if (isU && ur == j)
-                U = uc == j ? sd : U * inv;
-            const bool below = isU && ur > j;
-            const double ar = shfl_d(U, below ? tri_off(j) + ur - j : 0);
-            const double ac = shfl_d(U, below ? tri_off(j) + uc - j : 0);
-            if (below)
-                U -= ar * ac;
-        }
-    }
-    if (ok) {
-        v = -shfl_d(tv, lane < 6 ? 21 + lane : 0);
+            rinv[j] = inv;
 #pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            const double yk = rlane(v, k) * rlane(rinv, k);
-            const double ukl = shfl_d(U, lane > k && lane < 6 ? tri_off(k) + lane - k : 0);
-            if (lane == k)
-                v = yk;
-            else if (lane > k && lane < 6)
-                v -= ukl * yk;
+            for (int c = j + 1; c < 6; ++c)
+                U[tri_off(j) + c - j] *= inv;
+#pragma unroll
+            for (int r = j + 1; r < 6; ++r)
+#pragma unroll
+                for (int c = r; c < 6; ++c)
+                    U[tri_off(r) + c - r] =
+                        fma(-U[tri_off(j) + r - j], U[tri_off(j) + c - j], U[tri_off(r) + c - r]);
+            // forward substitution as soon as row j is there
+            v[j] *= inv;
+#pragma unroll
+            for (int c = j + 1; c < 6; ++c)
+                v[c] = fma(-U[tri_off(j) + c - j], v[j], v[c]);
         }
 #pragma unroll
         for (int k = 5; k >= 0; --k) {
-            const double xk = rlane(v, k) * rlane(rinv, k);
-            const double ulk = shfl_d(U, lane < k ? tri_off(lane) + k - lane : 0);
-            if (lane == k)
-                v = xk;
-            else if (lane < k)
-                v -= ulk * xk;
+            v[k] *= rinv[k];
+#pragma unroll
+            for (int r = 0; r < k; ++r)
+                v[r] = fma(-U[tri_off(r) + k - r], v[k], v[r]);
         }
     }
     if (a.learned && a.mode == kStepNormal && (!ok || sum_w < 0.1 * (double)n_valid)) {
@@ -464,8 +439,7 @@ __device__ __forceinline__ bool solve_pair_wave(const StepArgs &a, int pair, int
         if (a.mode != kStepDebug && lane == 0)
             fl[l] = 1;
     } else {
-        const double w0 = rlane(v, 0), w1 = rlane(v, 1), w2 = rlane(v, 2);
-        const double t0 = rlane(v, 3), t1 = rlane(v, 4), t2 = rlane(v, 5);
+        const double w0 = v[0], w1 = v[1], w2 = v[2], t0 = v[3], t1 = v[4], t2 = v[5];
         srot = sqrt(w0 * w0 + w1 * w1 + w2 * w2);
         stra = sqrt(t0 * t0 + t1 * t1 + t2 * t2);
         if (a.mode != kStepDebug) {
@@ -518,9 +492,8 @@ __device__ __forceinline__ bool solve_pair_wave(const StepArgs &a, int pair, int
                 fl[l] = 1;
         }
     }
-    const double gj = shfl_d(tv, lane < 6 ? 21 + lane : 0);  // all lanes exchange
-    if (lane < 6)
-        out->Jtr[lane] = gj;
+    if (lane >= 21 && lane < 27)
+        out->Jtr[lane - 21] = tv;
     if (lane == 0) {
         out->status = status;
         out->iters_run = a.iter + 1;
@@ -797,6 +770,23 @@ __device__ __forceinline__ void step_segments(const StepArgs &a, const MlpInfer 
     }
 }
 
+// Count k (0 valid, 1 inlier, 2 projected) summed over the NW wavefronts of
+// step_segments: the valid counts are the sums' entry 30, the others
+// integers; one strided read per wavefront either way, so that lanes of
+// different k stay together (a branch per wavefront cost 3000 cycles of 16).
+template <int NW, typename T>
+__device__ __forceinline__ int wave_counts(const T (*s_wave)[kAccum], const int (*s_wcnt)[4], int k)
+{
+    int c = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const T v = s_wave[w][30];
+        const int n = s_wcnt[w][k];
+        c += k == 0 ? (int)v : n;
+    }
+    return c;
+}
+
 template <typename T, bool COHERENT>
 __device__ __forceinline__ void solve_from_tiles(const StepArgs &a, int pair, int *fl);
 
@@ -855,6 +845,8 @@ __global__ __launch_bounds__(256) void k_icp_step(StepArgs a)
         step_segments<T, WMODE, CHUNK, LEAN, false>(a, F, pair, tl.y, min(tl.y + a.tile_seg, Hl * spr),
                                                     a.stats_pass != 0, pose, pfr, s_wave, s_wcnt);
         __syncthreads();
+        // the record and the ticket are the first wavefront's alone: between
+        // them it waits for its own stores, not for the workgroup
         if (tid < kAccum) {
             T sum = (T)0;
             for (int w = 0; w < nwave; ++w)
@@ -864,21 +856,18 @@ __global__ __launch_bounds__(256) void k_icp_step(StepArgs a)
                 __hip_atomic_store(dst, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             else
                 *dst = sum;
-        } else if (tid == kAccum) {
-            int4 c = make_int4(0, 0, 0, 0);
+        } else if (tid < kAccum + 4) {
+            const int k = tid - kAccum;  // 3: padding
+            int c = 0;
             for (int w = 0; w < nwave; ++w) {
-                c.x += (int)s_wave[w][30];
-                c.y += s_wcnt[w][1];
-                c.z += s_wcnt[w][2];
+                const int v = (int)s_wave[w][30], n = k < 3 ? s_wcnt[w][k] : 0;
+                c += k == 0 ? v : n;
             }
-            if constexpr (FUSED) {
-                int *dst = reinterpret_cast<int *>(a.pcnt + cur);
-                __hip_atomic_store(dst + 0, c.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(dst + 1, c.y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(dst + 2, c.z, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            } else {
-                a.pcnt[cur] = c;
-            }
+            int *dst = reinterpret_cast<int *>(a.pcnt + cur) + k;
+            if constexpr (FUSED)
+                __hip_atomic_store(dst, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            else
+                *dst = c;
         }
         if constexpr (FUSED) {
             // The record is written with agent-scope (device-coherent) stores;
@@ -888,11 +877,15 @@ __global__ __launch_bounds__(256) void k_icp_step(StepArgs a)
             // (the order of the sum does not depend on which workgroup that
             // is), then resets the pair's ticket count for the next launch.
             // No workgroup waits for another, and no cache is flushed.
-            __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the record stores are complete
-            __syncthreads();
-            if (tid == 0) {
-                const int t = __hip_atomic_fetch_add(a.tickets + pair, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                s_last = t == cload(&P->ntile[l]) - 1 ? 1 : 0;
+            if (tid < 64) {
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the record stores are complete
+                asm volatile("" ::: "memory");
+                if (tid == 0) {
+                    const int t =
+                        __hip_atomic_fetch_add(a.tickets + pair, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    s_last = t == cload(&P->ntile[l]) - 1 ? 1 : 0;
+                }
             }
             __syncthreads();
             if (s_last) {
@@ -933,7 +926,7 @@ __global__ __launch_bounds__(kPairBlock) void k_icp_level(StepArgs a)
     __shared__ long long s_cnt[4];
     __shared__ double s_pose[12];
     __shared__ int s_go;
-    const int pair = a.pair_base + blockIdx.x, tid = threadIdx.x, nwave = blockDim.x >> 6, l = a.level;
+    const int pair = a.pair_base + blockIdx.x, tid = threadIdx.x, l = a.level;
     int *fl = a.flags + (size_t)pair * kFlagStride;
     const PairDesc<T> *P = reinterpret_cast<const PairDesc<T> *>(a.pairs) + pair;
     if (cload(&P->ntile[l]) != 0 || (cload(fl + l) & 1))
@@ -960,16 +953,20 @@ __global__ __launch_bounds__(kPairBlock) void k_icp_level(StepArgs a)
         const bool last = it == a.iters - 1;
         step_segments<T, 0, CHUNK, true, true>(a, F, pair, 0, Hl * spr, last, pose, s_fr, s_wave, s_wcnt);
         __syncthreads();
+        // (constant counts: all shared-memory reads go out together)
+        constexpr int kWaves = kPairBlock / 64;
         if (tid < kAccum) {
+            T p[kWaves];
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w)
+                p[w] = s_wave[w][tid];
             double t = 0.0;
-            for (int w = 0; w < nwave; ++w)
-                t += (double)s_wave[w][tid];
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w)
+                t += (double)p[w];
             s_tot[tid] = t;
         } else if (tid >= 64 && tid < 67) {
-            long long c = 0;
-            for (int w = 0; w < nwave; ++w)
-                c += tid == 64 ? (long long)s_wave[w][30] : (long long)s_wcnt[w][tid - 64];
-            s_cnt[tid - 64] = c;
+            s_cnt[tid - 64] = wave_counts<kWaves>(s_wave, s_wcnt, tid - 64);
         }
         __syncthreads();
         if (tid < 64) {
