@@ -433,7 +433,6 @@ struct Plan {
     // tile records; level l's start at record rec0[l] (levels never share
     // records: sub-batches may be at different levels at the same time)
     void *d_psum = nullptr;
-    int4 *d_pcnt = nullptr;
     int rec0[kMaxLevels] = {};
     double *d_poses = nullptr;
     rir_level_stats *d_stats = nullptr;
@@ -826,7 +825,6 @@ rir_status make_plan(rir_ctx *ctx, const PlanKey &key, const rir_pair *pairs, in
     for (int l = 0; l < L; ++l)
         o_tiles[l] = lay.add(sizeof(int2) * tiles[l].size());
     size_t o_psum = lay.add((size_t)max_tiles * kAccum * tsz);
-    size_t o_pcnt = lay.add((size_t)max_tiles * sizeof(int4));
     size_t o_pose = lay.add((size_t)n * 16 * sizeof(double));
     size_t o_stats = lay.add((size_t)n * L * sizeof(rir_level_stats));
     size_t o_flags = lay.add((size_t)(n * kFlagStride + n) * sizeof(int));  // flags, then tickets
@@ -869,7 +867,6 @@ rir_status make_plan(rir_ctx *ctx, const PlanKey &key, const rir_pair *pairs, in
         HIP_TRY(hipMemcpy(P->d_tiles[l], tiles[l].data(), sizeof(int2) * tiles[l].size(), hipMemcpyHostToDevice));
     }
     P->d_psum = base + o_psum;
-    P->d_pcnt = reinterpret_cast<int4 *>(base + o_pcnt);
     P->d_poses = reinterpret_cast<double *>(base + o_pose);
     P->d_stats = reinterpret_cast<rir_level_stats *>(base + o_stats);
     P->d_flags = reinterpret_cast<int *>(base + o_flags);
@@ -1051,7 +1048,6 @@ StepArgs step_args(const Plan *P, const rir_icp_params *p, int level, int iter, 
     a.lean = (mode != kStepDebug && P->lean[level]) ? 1 : 0;
     a.learned = learned_at(p, level) ? 1 : 0;
     a.psum = static_cast<char *>(P->d_psum) + (size_t)P->rec0[level] * kAccum * (P->fp64 ? sizeof(double) : sizeof(float));
-    a.pcnt = P->d_pcnt + P->rec0[level];
     a.poses = P->d_poses;
     a.stats = P->d_stats;
     a.flags = P->d_flags;
@@ -1067,16 +1063,17 @@ StepArgs step_args(const Plan *P, const rir_icp_params *p, int level, int iter, 
     return a;
 }
 
-// Enqueues the flag/ticket/statistics reset of the whole batch.
-rir_status enqueue_clear(const Plan *P, hipStream_t st)
+// Enqueues the flag/ticket/statistics reset of the whole batch and, unless the
+// prepass sets the poses, the ray frames of the poses it starts from.
+rir_status enqueue_begin(const Plan *P, const rir_icp_params *p, hipStream_t st)
 {
-    HIP_TRY(launch_clear(P->d_flags, P->n_pairs * (kFlagStride + 1), P->d_stats, P->n_pairs * P->key.k.levels, st));
+    HIP_TRY(launch_begin(P->fp64, step_args(P, p, 0, 0, kStepNormal), P->n_pairs, p->init_mode == 0, st));
     return RIR_OK;
 }
 
 // Enqueues the normal/pyramid pass (target records, level images, learned
-// neighbour features, initial pose and ray frames) of the whole batch
-// (lane < 0) or of one sub-batch.
+// neighbour features and, with the centroid initialisation, the initial poses
+// and their ray frames) of the whole batch (lane < 0) or of one sub-batch.
 rir_status enqueue_prepass(const Plan *P, const rir_icp_params *p, hipStream_t st, int lane = -1)
 {
     const int np = lane < 0 ? P->n_pairs : P->lane_p0[lane + 1] - P->lane_p0[lane];
@@ -1111,8 +1108,6 @@ rir_status enqueue_prepass(const Plan *P, const rir_icp_params *p, hipStream_t s
             b.delta = p->delta;
             HIP_TRY(launch_nbr_feats(b, np, (int)P->max_px[l], st));
         }
-    StepArgs f = step_args(P, p, 0, 0, kStepNormal, lane);
-    HIP_TRY(launch_frames(P->fp64, f, np, st));
     return RIR_OK;
 }
 
@@ -1211,7 +1206,7 @@ rir_status enqueue_all(rir_ctx *ctx, Plan *P, const rir_icp_params *p, int timin
     const bool lanes = P->n_lanes > 1, fine_lanes = lanes && P->key.k.tune.lane_fine;
     if (timed_part(timing, L) && (s = record_timing(evs[2 * L], st, capturing)) != RIR_OK)
         return s;
-    if ((s = enqueue_clear(P, st)) != RIR_OK)
+    if ((s = enqueue_begin(P, p, st)) != RIR_OK)
         return s;
     if (lanes && timing == 0)
         s = enqueue_lanes(ctx, P, p, true, L - 1, fine_lanes ? 0 : 1, st);
@@ -1405,7 +1400,7 @@ extern "C" rir_status rir_debug_associate(rir_ctx *ctx, const rir_icp_params *pa
     s = update_images(P, pair, st);
     if (s != RIR_OK)
         return s;
-    s = enqueue_clear(P, st);
+    s = enqueue_begin(P, &q, st);
     if (s == RIR_OK)
         s = enqueue_prepass(P, &q, st);
     if (s != RIR_OK)

@@ -14,6 +14,7 @@
 // No floating-point atomics: results are bitwise reproducible for a fixed
 // tuning.
 #include <float.h>
+#include <type_traits>
 
 #include "rir_internal.h"
 #include "rir_mlp_device.h"
@@ -147,17 +148,6 @@ __global__ void k_normals(SensorTab<float> S, const float *range, double edge_re
     }
 }
 
-__global__ void k_clear(int *flags, int n_flags, rir_level_stats *stats, int n_stats)
-{
-    const int tid = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
-    for (int i = tid; i < n_flags; i += nt)
-        flags[i] = 0;
-    int *sw = reinterpret_cast<int *>(stats);
-    const int nw = n_stats * (int)(sizeof(rir_level_stats) / sizeof(int));
-    for (int i = tid; i < nw; i += nt)
-        sw[i] = 0;
-}
-
 // ----------------------------------------------------------------------------- prepass
 
 // Normal image and pyramid (Sec. 4.1): each wavefront takes kPrepSeg
@@ -284,35 +274,6 @@ __global__ __launch_bounds__(256) void k_prepass(PrepArgs a)
             psum[(size_t)cur * kAccum + tid] = sum;
         }
         __syncthreads();
-    }
-}
-
-// Initial pose from the point-set centres (Sec. 4.1): R = I and
-// t = mean(valid target points) - mean(valid source points), from the tile
-// sums of the prepass, added in FP64 in tile order.  One wave per pair.
-template <typename T>
-__global__ __launch_bounds__(64) void k_centroid(PrepArgs a)
-{
-    __shared__ double s_c[8];
-    const int pair = a.pair_base + blockIdx.x;
-    const PairDesc<T> &P = reinterpret_cast<const PairDesc<T> *>(a.pairs)[pair];
-    const T *psum = reinterpret_cast<const T *>(a.psum);
-    const int lane = threadIdx.x;
-    if (lane < 8) {
-        double s = 0.0;
-        for (int k = 0; k < P.ntile[0]; ++k)
-            s += (double)psum[(size_t)(P.tile0[0] + k) * kAccum + lane];
-        s_c[lane] = s;
-    }
-    __syncthreads();
-    if (lane < 16) {
-        double *T0 = a.poses + 16 * (size_t)pair;
-        double val = (lane % 5 == 0) ? 1.0 : 0.0;
-        if ((lane == 3 || lane == 7 || lane == 11) && s_c[3] > 0.0 && s_c[7] > 0.0) {
-            const int c = lane / 4;
-            val = s_c[4 + c] / s_c[7] - s_c[c] / s_c[3];
-        }
-        T0[lane] = val;
     }
 }
 
@@ -584,6 +545,7 @@ __device__ __forceinline__ void step_segments(const StepArgs &a, const MlpInfer 
     const T r00 = pose[0], r01 = pose[1], r10 = pose[4], r11 = pose[5], r20 = pose[8], r21 = pose[9];
     const T t0 = pose[3], t1 = pose[7], t2 = pose[11];
     const int Wl = V.Wl, Hl = V.Hl, spr = (Wl + kSegPx - 1) / kSegPx;
+    const int lg_spr = 31 - __builtin_clz((unsigned)spr);  // LEAN: spr is a power of two
     const uint32_t npx = (uint32_t)(Hl * Wl);
     const rsrc_t srs = make_rsrc(cload(&P->src[l]), npx * 4u);
     const rsrc_t drs = make_rsrc(cload(&P->dst4[l]), npx * (uint32_t)(4 * sizeof(T)));
@@ -604,8 +566,8 @@ __device__ __forceinline__ void step_segments(const StepArgs &a, const MlpInfer 
         for (int j = 0; j < CHUNK; ++j) {
             const int seg = s0 + j * nwave;
             const bool live = seg < seg_end;
-            const int v = live ? seg / spr : 0;
-            const int u0 = (seg - v * spr) * kSegPx, u = u0 + lane;
+            const int v = live ? (LEAN ? seg >> lg_spr : seg / spr) : 0;
+            const int u0 = (seg - (LEAN ? v << lg_spr : v * spr)) * kSegPx, u = u0 + lane;
             vs[j] = v;
             us[j] = u;
             if constexpr (LEAN) {
@@ -787,6 +749,15 @@ __device__ __forceinline__ int wave_counts(const T (*s_wave)[kAccum], const int 
     return c;
 }
 
+// A record entry that holds two 16-bit counts as its bit pattern.
+template <typename T>
+__device__ __forceinline__ T count_bits(uint32_t c);
+template <>
+__device__ __forceinline__ float count_bits<float>(uint32_t c) { return __builtin_bit_cast(float, c); }
+template <>
+__device__ __forceinline__ double count_bits<double>(uint32_t c) { return __builtin_bit_cast(double, (uint64_t)c); }
+static_assert(kTileMaxPx < 65536, "tile counts fit 16 bits");
+
 template <typename T, bool COHERENT>
 __device__ __forceinline__ void solve_from_tiles(const StepArgs &a, int pair, int *fl);
 
@@ -846,28 +817,23 @@ __global__ __launch_bounds__(256) void k_icp_step(StepArgs a)
                                                     a.stats_pass != 0, pose, pfr, s_wave, s_wcnt);
         __syncthreads();
         // the record and the ticket are the first wavefront's alone: between
-        // them it waits for its own stores, not for the workgroup
+        // them it waits for its own stores, not for the workgroup.  Entry 30
+        // is the valid count, entry 31 the bits of the inlier and projection
+        // counts (kTileMaxPx bounds them)
         if (tid < kAccum) {
             T sum = (T)0;
-            for (int w = 0; w < nwave; ++w)
+            uint32_t counts = 0;
+            for (int w = 0; w < nwave; ++w) {
                 sum += s_wave[w][tid];
+                counts += (uint32_t)s_wcnt[w][1] | (uint32_t)s_wcnt[w][2] << 16;
+            }
+            if (tid == 31)
+                sum = count_bits<T>(counts);
             T *dst = psum + (size_t)cur * kAccum + tid;
             if constexpr (FUSED)
                 __hip_atomic_store(dst, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             else
                 *dst = sum;
-        } else if (tid < kAccum + 4) {
-            const int k = tid - kAccum;  // 3: padding
-            int c = 0;
-            for (int w = 0; w < nwave; ++w) {
-                const int v = (int)s_wave[w][30], n = k < 3 ? s_wcnt[w][k] : 0;
-                c += k == 0 ? v : n;
-            }
-            int *dst = reinterpret_cast<int *>(a.pcnt + cur) + k;
-            if constexpr (FUSED)
-                __hip_atomic_store(dst, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            else
-                *dst = c;
         }
         if constexpr (FUSED) {
             // The record is written with agent-scope (device-coherent) stores;
@@ -990,8 +956,80 @@ __global__ __launch_bounds__(kPairBlock) void k_icp_level(StepArgs a)
 
 // ----------------------------------------------------------------------------- solve kernels
 
-// Frames for the current poses of all pairs (after the poses are set from
-// the host or by the centroid initialisation).  One workgroup per pair.
+// Initial pose from the point-set centres (Sec. 4.1): R = I and
+// t = mean(valid target points) - mean(valid source points), from the tile
+// sums of the prepass, added in FP64 in tile order, and the ray frames of that
+// pose.  One wave per pair; 16 tiles' sums are in flight at a time (32 tiles
+// one after the other took 10.7 us).
+template <typename T>
+__global__ __launch_bounds__(64) void k_centroid(PrepArgs a)
+{
+    __shared__ double s_c[8];
+    const int pair = a.pair_base + blockIdx.x;
+    const PairDesc<T> *P = reinterpret_cast<const PairDesc<T> *>(a.pairs) + pair;
+    const int lane = threadIdx.x;
+    if (lane < 8) {
+        const int nt = cload(&P->ntile[0]);
+        const T *q = reinterpret_cast<const T *>(a.psum) + (size_t)cload(&P->tile0[0]) * kAccum + lane;
+        double s = 0.0;
+        for (int k = 0; k < nt; k += 16) {
+            T v[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                v[i] = k + i < nt ? q[(size_t)(k + i) * kAccum] : (T)0;
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                s += (double)v[i];
+        }
+        s_c[lane] = s;
+    }
+    __syncthreads();
+    double R[12];
+#pragma unroll
+    for (int k = 0; k < 12; ++k)
+        R[k] = k % 5 == 0 ? 1.0 : 0.0;
+    if (s_c[3] > 0.0 && s_c[7] > 0.0) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            R[4 * c + 3] = s_c[4 + c] / s_c[7] - s_c[c] / s_c[3];
+    }
+    if (lane < 16) {
+        double val = lane % 5 == 0 ? 1.0 : 0.0;
+        val = lane == 3 ? R[3] : (lane == 7 ? R[7] : (lane == 11 ? R[11] : val));
+        a.poses[16 * (size_t)pair + lane] = val;
+    }
+    write_frames(P, R);
+}
+
+// The start of a batch, one workgroup per pair: the pair's flags, ticket count
+// and statistics cleared and, with frames (the poses are set already, not by
+// the centroid initialisation), the ray frames of its pose.  As a clearing
+// launch before the prepass and a frames launch after it the two took 5 us
+// more of a call.
+template <typename T>
+__global__ __launch_bounds__(256) void k_begin(StepArgs a, int frames)
+{
+    const int pair = a.pair_base + blockIdx.x, tid = threadIdx.x;
+    if (tid < kFlagStride)
+        a.flags[(size_t)pair * kFlagStride + tid] = 0;
+    if (tid == kFlagStride)
+        a.tickets[pair] = 0;
+    int *sw = reinterpret_cast<int *>(a.stats + (size_t)pair * a.levels);
+    const int nw = a.levels * (int)(sizeof(rir_level_stats) / sizeof(int));
+    for (int i = tid; i < nw; i += blockDim.x)
+        sw[i] = 0;
+    if (!frames)
+        return;
+    const PairDesc<T> *P = reinterpret_cast<const PairDesc<T> *>(a.pairs) + pair;
+    double R[12];
+#pragma unroll
+    for (int k = 0; k < 12; ++k)
+        R[k] = a.poses[16 * (size_t)pair + k];
+    write_frames(P, R);
+}
+
+// Frames for the current poses of all pairs (the debug pass, whose pose comes
+// after the prepass).  One workgroup per pair.
 template <typename T>
 __global__ __launch_bounds__(256) void k_frames(StepArgs a)
 {
@@ -1004,75 +1042,81 @@ __global__ __launch_bounds__(256) void k_frames(StepArgs a)
     write_frames(P, R);
 }
 
+// Adds entry off of N records, 8 records apart, in order: the entry as a
+// number, and its low bits as two counts.  All N loads go out together.
+template <typename T, bool COHERENT, int N>
+__device__ __forceinline__ void add_records(rsrc_t recs, uint32_t off, double &sum, uint32_t &c1, uint32_t &c2)
+{
+    T v[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const uint32_t o = off + 8u * (uint32_t)(kAccum * sizeof(T)) * (uint32_t)i;
+        if constexpr (COHERENT)
+            v[i] = bld1_agent<T>(recs, o);
+        else
+            v[i] = bld1<T>(recs, o);
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        sum += (double)v[i];
+        c1 += low_bits(v[i]) & 0xffffu;
+        c2 += low_bits(v[i]) >> 16;
+    }
+}
+
 // Sum of one pair's tile records t0 .. t0 + nt - 1 in FP64 in a fixed order
 // that does not depend on the batch or the block size: group g (of 8) of 32
-// threads, one per record entry, adds tiles g, g + 8, ... in that order (four
-// records in flight at a time), then the 8 group sums are added in group
-// order.  Leaves the 30 sums in s_tot and the 3 counts in s_cnt; all threads
-// of the block (64..256) take part.  COHERENT reads the records with
-// agent-scope loads (records written during the same launch by other
-// workgroups, see k_icp_step).
+// threads, one per record entry, adds tiles g, g + 8, ... in that order, then
+// the 8 group sums are added in group order.  Leaves the 30 sums in s_tot and
+// the 3 counts in s_cnt; all threads of the block (64..256) take part.
+// COHERENT reads the records with agent-scope loads (records written during
+// the same launch by other workgroups, see k_icp_step).  Bound by the latency
+// of those loads (about 1800 cycles a round trip): up to 16 records a group
+// are in flight, one round trip for the 128 tiles of a 128x2048 level 0
+// (7400 -> 2600 cycles against four at a time, with the counts in
+// loads of their own).
 template <typename T, bool COHERENT>
 __device__ __forceinline__ void reduce_pair_tiles(const StepArgs &a, int t0, int nt, double (*s_part)[kAccum],
-                                                  long long (*s_cpart)[4], double *s_tot, long long *s_cnt)
+                                                  uint32_t (*s_cpart)[2], double *s_tot, long long *s_cnt)
 {
-    const T *psum = reinterpret_cast<const T *>(a.psum);
-    const int *pcnt = reinterpret_cast<const int *>(a.pcnt);
+    constexpr uint32_t kRec = kAccum * sizeof(T);  // bytes of a record
+    const rsrc_t recs = make_rsrc(reinterpret_cast<const T *>(a.psum) + (size_t)t0 * kAccum, (uint32_t)nt * kRec);
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));  // see solve_pair_wave
     const int comp = tid & 31;
-    auto rec = [&](int k) -> T {
-        const T *q = psum + (size_t)(t0 + k) * kAccum + comp;
-        if constexpr (COHERENT)
-            return __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        else
-            return *q;
-    };
-    auto cnt_of = [&](int k) -> int {
-        const int *q = pcnt + 4 * (size_t)(t0 + k) + comp;
-        if constexpr (COHERENT)
-            return __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        else
-            return *q;
-    };
     for (int grp = tid >> 5; grp < 8; grp += (int)(blockDim.x >> 5)) {
         double sum = 0.0;
-        long long c = 0;
-        int k = grp;
-        for (; k + 24 < nt; k += 32) {
-            const T v0 = rec(k), v1 = rec(k + 8), v2 = rec(k + 16), v3 = rec(k + 24);
-            if (comp < 3) {
-                const int c0 = cnt_of(k), c1 = cnt_of(k + 8), c2 = cnt_of(k + 16), c3 = cnt_of(k + 24);
-                c += c0;
-                c += c1;
-                c += c2;
-                c += c3;
-            }
-            sum += (double)v0;
-            sum += (double)v1;
-            sum += (double)v2;
-            sum += (double)v3;
-        }
-        for (; k < nt; k += 8) {
-            sum += (double)rec(k);
-            if (comp < 3)
-                c += cnt_of(k);
+        uint32_t c1 = 0, c2 = 0;
+        // (records beyond the pair's read 0: the descriptor ends there)
+        const uint32_t off = (uint32_t)grp * kRec + (uint32_t)comp * (uint32_t)sizeof(T);
+        if (nt <= 32) {
+            add_records<T, COHERENT, 4>(recs, off, sum, c1, c2);
+        } else {
+            for (int k = 0; k < nt; k += 128)
+                add_records<T, COHERENT, 16>(recs, off + (uint32_t)k * kRec, sum, c1, c2);
         }
         s_part[grp][comp] = sum;
-        if (comp < 3)
-            s_cpart[grp][comp] = c;
+        if (comp == 31) {  // its sum is of bit patterns, unused
+            s_cpart[grp][0] = c1;
+            s_cpart[grp][1] = c2;
+        }
     }
     __syncthreads();
-    if (tid < 30) {
+    if (tid < 31) {
         double t = 0.0;
+#pragma unroll
         for (int g = 0; g < 8; ++g)
             t += s_part[g][tid];
-        s_tot[tid] = t;
-    } else if (tid >= 32 && tid < 35) {
+        if (tid < 30)
+            s_tot[tid] = t;
+        else
+            s_cnt[0] = (long long)t;
+    } else if (tid >= 32 && tid < 34) {
         long long t = 0;
+#pragma unroll
         for (int g = 0; g < 8; ++g)
             t += s_cpart[g][tid - 32];
-        s_cnt[tid - 32] = t;
+        s_cnt[tid - 31] = t;
     }
     __syncthreads();
 }
@@ -1085,7 +1129,7 @@ template <typename T, bool COHERENT>
 __device__ __forceinline__ void solve_from_tiles(const StepArgs &a, int pair, int *fl)
 {
     __shared__ double s_part[8][kAccum];
-    __shared__ long long s_cpart[8][4];
+    __shared__ uint32_t s_cpart[8][2];
     __shared__ double s_tot[32];
     __shared__ long long s_cnt[4];
     __shared__ double s_pose[12];
@@ -1159,11 +1203,12 @@ hipError_t launch_normals(const SensorTab<float> &S, const float *range, double 
     return hipGetLastError();
 }
 
-hipError_t launch_clear(int *flags, int n_flags, rir_level_stats *stats, int n_stats, hipStream_t stream)
+hipError_t launch_begin(bool fp64, const StepArgs &a, int n_pairs, bool frames, hipStream_t stream)
 {
-    int64_t nw = (int64_t)n_stats * (int64_t)(sizeof(rir_level_stats) / sizeof(int));
-    int64_t n = nw > n_flags ? nw : n_flags;
-    hipLaunchKernelGGL(k_clear, dim3(grid_for(n, 256)), dim3(256), 0, stream, flags, n_flags, stats, n_stats);
+    if (fp64)
+        hipLaunchKernelGGL(k_begin<double>, dim3(n_pairs), dim3(256), 0, stream, a, frames ? 1 : 0);
+    else
+        hipLaunchKernelGGL(k_begin<float>, dim3(n_pairs), dim3(256), 0, stream, a, frames ? 1 : 0);
     return hipGetLastError();
 }
 

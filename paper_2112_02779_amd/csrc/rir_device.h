@@ -129,6 +129,21 @@ __device__ __forceinline__ double bld1<double>(rsrc_t r, uint32_t off)
     return __builtin_bit_cast(double, lo | (hi << 32));
 }
 
+// The same past the caches of the issuing XCD (the sc1 bit, agent scope), for
+// data that other workgroups wrote during the running launch.
+template <typename T>
+__device__ __forceinline__ T bld1_agent(rsrc_t r, uint32_t off)
+{
+    constexpr int kSc1 = 16;
+    const uint32_t lo = __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, kSc1);
+    if constexpr (sizeof(T) == 4) {
+        return __builtin_bit_cast(T, lo);
+    } else {
+        const uint64_t hi = __builtin_amdgcn_raw_buffer_load_b32(r, off + 4u, 0, kSc1);
+        return __builtin_bit_cast(T, (uint64_t)lo | (hi << 32));
+    }
+}
+
 template <typename T>
 __device__ __forceinline__ void bld2(rsrc_t r, uint32_t off, T &a, T &b)
 {

@@ -62,7 +62,8 @@ struct LevelImage {
 constexpr int kFlagStride = kMaxLevels + 1;
 // Concurrent sub-batches (streams) of the coarse levels of one batch.
 constexpr int kMaxLanes = 4;
-constexpr int kAccum = 32;  // float accumulators per tile (30 used)
+constexpr int kAccum = 32;  // record entries per tile
+constexpr int kTileMaxPx = 256 * 16;  // pixels of the largest tile a tuning gives
 
 enum StepMode { kStepNormal = 0, kStepFallback = 1, kStepDebug = 2 };
 
@@ -97,8 +98,8 @@ struct StepArgs {
     int fused;           // 1: the workgroup that finishes a pair's last tile
                          // solves that pair (no separate solve launch)
     int *tickets;        // [n_pairs] tiles finished in this launch (fused)
-    void *psum;          // T[n_tiles][kAccum]
-    int4 *pcnt;          // [n_tiles] (n_valid, n_inlier, n_proj, 0)
+    void *psum;          // T[n_tiles][kAccum]: 30 sums, the valid count, and the
+                         // bits n_inlier | n_proj << 16
     double *poses;       // [n_pairs][16]
     rir_level_stats *stats;  // [n_pairs][levels] (debug: [1])
     int *flags;          // [n_pairs][kFlagStride]
@@ -145,7 +146,9 @@ hipError_t launch_project(const SensorTab<float> *tab, int level, const float *x
                           float *r, uint8_t *valid, hipStream_t stream);
 hipError_t launch_normals(const SensorTab<float> &S, const float *range, double edge_rel, float *nrm,
                           uint8_t *valid, hipStream_t stream);
-hipError_t launch_clear(int *flags, int n_flags, rir_level_stats *stats, int n_stats, hipStream_t stream);
+// Clears the flags, tickets and statistics of every pair; frames: also writes
+// the ray frames of the current poses.
+hipError_t launch_begin(bool fp64, const StepArgs &a, int n_pairs, bool frames, hipStream_t stream);
 hipError_t launch_prepass(bool fp64, const PrepArgs &a, int grid, int block, int n_pairs, hipStream_t stream);
 // Level-0 target records (n, n . q) from PCA normals of the (2 half + 1)^2
 // window (normals_pca.hip) for every pair; max_px: the largest level-0 image.
