@@ -440,6 +440,7 @@ struct Plan {
     int *d_tickets = nullptr;  // [n_pairs], right after the flags
     bool nbf[kMaxLevels] = {};       // level keeps the learned weight's neighbour features
     size_t max_px[kMaxLevels] = {};  // largest level image of the batch
+    int pca_tiles = 0;               // most PCA tiles of an image of the batch
     std::vector<const float *> cur_src, cur_dst;
     hipEvent_t desc_evt = nullptr;
     bool desc_pending = false;
@@ -858,6 +859,8 @@ rir_status make_plan(rir_ctx *ctx, const PlanKey &key, const rir_pair *pairs, in
             P->max_px[l] = std::max<size_t>(P->max_px[l], Nl);
         }
     }
+    for (int i = 0; i < n; ++i)
+        P->pca_tiles = std::max(P->pca_tiles, pca_tiles(pairs[i].sensor->H, pairs[i].sensor->W));
     HIP_TRY(hipMalloc(&P->dmem, lay.bytes));
     char *base = static_cast<char *>(P->dmem);
     HIP_TRY(hipMemset(base + o_flags, 0, (size_t)(n * kFlagStride + n) * sizeof(int)));
@@ -1097,7 +1100,7 @@ rir_status enqueue_prepass(const Plan *P, const rir_icp_params *p, hipStream_t s
     a.xcd_remap = P->key.k.tune.xcd_remap;
     a.given_normals = P->key.k.normal_window > 0 ? 1 : 0;
     if (a.given_normals)
-        HIP_TRY(launch_pca_records(P->fp64, a, P->key.k.normal_window, np, (int)P->max_px[0], st));
+        HIP_TRY(launch_pca_records(P->fp64, a, P->key.k.normal_window, np, P->pca_tiles, st));
     HIP_TRY(launch_prepass(P->fp64, a, lane < 0 ? P->grid[0] : P->lane_grid[0][lane], P->block, np, st));
     for (int l = 0; l < P->key.k.levels; ++l)
         if (P->nbf[l]) {

@@ -151,8 +151,10 @@ hipError_t launch_normals(const SensorTab<float> &S, const float *range, double 
 hipError_t launch_begin(bool fp64, const StepArgs &a, int n_pairs, bool frames, hipStream_t stream);
 hipError_t launch_prepass(bool fp64, const PrepArgs &a, int grid, int block, int n_pairs, hipStream_t stream);
 // Level-0 target records (n, n . q) from PCA normals of the (2 half + 1)^2
-// window (normals_pca.hip) for every pair; max_px: the largest level-0 image.
-hipError_t launch_pca_records(bool fp64, const PrepArgs &a, int half, int n_pairs, int max_px, hipStream_t stream);
+// window (normals_pca.hip) for every pair; max_tiles: the largest pca_tiles of
+// the batch's images.
+int pca_tiles(int H, int W);
+hipError_t launch_pca_records(bool fp64, const PrepArgs &a, int half, int n_pairs, int max_tiles, hipStream_t stream);
 // Neighbour features of level a.level for every pair with an nbf image there
 // (FP32 instances only); max_px: the largest level image of the batch.
 hipError_t launch_nbr_feats(const NbrArgs &a, int n_pairs, int max_px, hipStream_t stream);
