@@ -23,15 +23,6 @@ namespace rir {
 
 namespace {
 
-// 1 / sqrt(x), x > 0 normal, to FP64 rounding error: the hardware's estimate
-// and two Newton steps.
-__device__ __forceinline__ double rsqrt64(double x)
-{
-    double y = __builtin_amdgcn_rsq(x);
-    y = y * fma(-0.5 * x * y, y, 1.5);
-    return y * fma(-0.5 * x * y, y, 1.5);
-}
-
 // The unit eigenvector n of the smallest eigenvalue of the symmetric matrix
 // [[a00 a01 a02] [a01 a11 a12] [a02 a12 a22]], if its middle eigenvalue exceeds
 // 1e-6 times the largest (else the points lie on a line) and it has two
@@ -54,7 +45,7 @@ __device__ __forceinline__ bool smallest_eigenvector(double a00, double a01, dou
     const double p2 = b00 * b00 + b11 * b11 + b22 * b22 + 2.0 * (s01 + s02 + s12);
     if (!(p2 > 0.0))
         return false;
-    const double h = p2 * (1.0 / 6.0), ip = rsqrt64(h), p = h * ip;
+    const double h = p2 * (1.0 / 6.0), ip = d_rsqrt(h), p = h * ip;
     const double det = b00 * (b11 * b22 - s12) - a01 * (a01 * b22 - a12 * a02) + a02 * (a01 * a12 - b11 * a02);
     double r = 0.5 * det * ip * ip * ip;
     r = r < -1.0 ? -1.0 : (r > 1.0 ? 1.0 : r);
@@ -94,7 +85,7 @@ __device__ __forceinline__ bool smallest_eigenvector(double a00, double a01, dou
     if (!(ss > 0.0))
         return false;
     // (tiny sums would leave the estimate's range)
-    const double inv = ss > 1e-290 ? rsqrt64(ss) : 1.0 / sqrt(ss);
+    const double inv = ss > 1e-290 ? d_rsqrt(ss) : 1.0 / sqrt(ss);
     n[0] = v0 * inv;
     n[1] = v1 * inv;
     n[2] = v2 * inv;
