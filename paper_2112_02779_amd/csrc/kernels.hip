@@ -613,8 +613,8 @@ __device__ __forceinline__ void step_segments(const StepArgs &a, const MlpInfer 
             }
             // a pixel without a return (0, negative, NaN, infinite) unprojects
             // at r = 0: its point is finite, so its exact-zero terms stay zero
-            const bool okr = range_ok(rs[j]);
-            const T r = okr ? (T)rs[j] : (T)0, c = ca[j], sn = sa[j], rc = r * c, rsn = r * sn;
+            proj[j] = range_ok(rs[j]);
+            const T r = proj[j] ? (T)rs[j] : (T)0, c = ca[j], sn = sa[j], rc = r * c, rsn = r * sn;
             xx[j] = fma(rc, f0.x, fma(rsn, f0.w, fma(r, f1.z, t0)));
             xy[j] = fma(rc, f0.y, fma(rsn, f1.x, fma(r, f1.w, t1)));
             xz[j] = fma(rc, f0.z, fma(rsn, f1.y, fma(r, f2.x, t2)));
@@ -623,8 +623,8 @@ __device__ __forceinline__ void step_segments(const StepArgs &a, const MlpInfer 
                 xy[j] += c * h1y + sn * h2y;
                 xz[j] += c * h1z + sn * h2z;
             }
-            proj[j] = project<T, !LEAN, LEAN>(V, xx[j], xy[j], xz[j], ul[j], vl[j], xr[j]) & okr;
         }
+        project_n<T, !LEAN, LEAN, CHUNK>(V, xx, xy, xz, ul, vl, xr, proj);
         // the gather needs no mask: project() keeps (ul, vl) inside the
         // level image for every lane, and a lane that did not project adds
         // exact zeros below whatever record it reads (w = 0, e = 0, finite J)
