@@ -25,6 +25,16 @@ struct SdfExtractArgs {
 
 constexpr int kNbrPerBlock = 7;
 
+// Workgroup w of a grid of xcd_grid(n) takes block xcd_block(w, n) (none if
+// >= n): workgroups go round robin to the 8 XCDs, so that each XCD, with a
+// cache of its own, gets a run of consecutive blocks.
+inline unsigned xcd_grid(int n) { return ((unsigned)n + 7u) / 8u * 8u; }
+__device__ __forceinline__ int xcd_block(unsigned w, int n)
+{
+    const uint64_t per = ((unsigned)n + 7u) / 8u, b = (w & 7u) * per + (w >> 3);
+    return (int)(b < (uint64_t)n ? b : (uint64_t)n);
+}
+
 // Exclusive prefix sum of v over a workgroup of 256 threads in thread order,
 // and the workgroup's total: inclusive sums within each wavefront by lane
 // exchanges, then the totals of the wavefronts before (s_wsum: 4 ints of

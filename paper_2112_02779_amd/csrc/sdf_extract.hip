@@ -4,40 +4,74 @@
 
 namespace rir {
 
-// Zero crossings of the fused SDF along the grid edges (the vertices of the
-// level set that Sec. 4.2 meshes with marching cubes).  One workgroup per
-// block: the block's 16^3 voxels and the first plane of its +x, +y and +z
-// neighbour blocks are staged in shared memory with independent loads
-// (outside the volume: weight -inf, no crossing); thread (x, y) then tests
-// the +x, +y and +z edges of every voxel of its column.  A crossing needs both
-// weights >= min_weight, SDF values on different sides of zero (s_a > 0 >=
-// s_b or the reverse) and |s_a - s_b| <= max_jump; its point
-// a + t (b - a), t = s_a / (s_a - s_b), is formed in FP64.  The workgroup
-// counts its crossings (a block without any stops there), takes one range of
-// the output with one atomic add, and writes its points there in thread
-// order (so the order of the points across blocks is not defined).
-__device__ __forceinline__ size_t vox_index(int nbx, int nby, int i, int j, int k)
-{
-    const size_t blk = ((size_t)(k >> 4) * nby + (j >> 4)) * nbx + (i >> 4);
-    return blk * (kSdfEdge * kSdfEdge * kSdfEdge) + (size_t)(((k & 15) * kSdfEdge + (j & 15)) * kSdfEdge + (i & 15));
-}
-
 __global__ void k_zero_u64(unsigned long long *p) { *p = 0ull; }
 
-constexpr int kE1 = kSdfEdge + 1;  // staged edge: the block plus one plane
-
-__device__ __forceinline__ bool crossing(const SdfExtractArgs &a, float2 A, float2 B)
+// The even and odd x of a row of 16 voxels come as one byte each.
+__device__ __forceinline__ uint32_t row_mask(const unsigned long long (&even)[32], const unsigned long long (&odd)[32],
+                                             int row)
 {
-    return B.y >= a.min_weight && (A.x > 0.f) != (B.x > 0.f) && !(fabs((double)A.x - (double)B.x) > a.max_jump);
+    return reinterpret_cast<const uint8_t *>(even)[row] | (uint32_t)reinterpret_cast<const uint8_t *>(odd)[row] << 8;
 }
 
+// Zero crossings of the fused SDF along the grid edges (the vertices of the
+// level set that Sec. 4.2 meshes with marching cubes).  One workgroup per
+// block of 16^3 voxels.  A crossing needs both weights >= min_weight, SDF
+// values on different sides of zero (s_a > 0 >= s_b or the reverse) and
+// |s_a - s_b| <= max_jump; its point a + t (b - a), t = s_a / (s_a - s_b), is
+// formed in FP64 (outside the volume: no crossing).
+//
+// Bound by reading the volume once.  So a voxel is reduced to two bits (valid,
+// positive) as it arrives, by ballots of the wavefront, and the block's masks
+// (1 KB) are all that is staged: thread (y, z) finds the crossings of its row
+// with a few operations on 16-bit words, the row's three edge directions
+// together.  The first planes of the +x, +y and +z neighbour blocks are read
+// only where a voxel beside them is valid; a block without a valid voxel ends
+// before that.  The few voxels at a crossing are read again (from a cache) for
+// the jump test and the points.  The workgroup takes one range of the output
+// with one atomic add and writes its points there in the order of thread
+// (x, y), then z, then axis (so the order of the points across blocks is not
+// defined).  Consecutive blocks go to one XCD, whose cache then holds their
+// common planes.  57 x 71 x 6 blocks (0.8 GB, 153 us at the copy rate): 250 ->
+// 175 us for a counting pass, 200 with the points (whole voxels staged in 39 KB of shared memory before).
 template <bool HASHED>
 __global__ __launch_bounds__(256) void k_sdf_extract(const SdfExtractArgs a)
 {
-    __shared__ float2 s_v[kE1][kE1][kE1];  // [z][y][x]
+    // [q * 4 + wavefront]: 8 rows each; row z * 16 + y
+    __shared__ unsigned long long s_ve[32], s_vo[32], s_pe[32], s_po[32];
+    __shared__ uint16_t s_fv[2][kSdfEdge], s_fp[2][kSdfEdge];  // +y plane by z, +z plane by y
+    __shared__ unsigned long long s_cross[kSdfEdge * kSdfEdge];  // 16 bits per axis
     __shared__ int s_wsum[4];
     __shared__ unsigned long long s_base;
-    const int b = blockIdx.x;
+    const int n_blocks = HASHED ? a.n_blocks : a.nbx * a.nby * a.nbz;
+    const int b = xcd_block(blockIdx.x, n_blocks);
+    if (b >= n_blocks)
+        return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const float2 *vox = reinterpret_cast<const float2 *>(a.vox);
+    constexpr size_t kB = kSdfEdge * kSdfEdge * kSdfEdge;
+    // the block: 4096 voxels, contiguous, two per 16-byte load
+    const float4 *blk = reinterpret_cast<const float4 *>(vox + (size_t)b * kB);
+    float4 w[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+        w[q] = blk[q * 256 + tid];
+    bool some = false;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const bool ve = w[q].y >= a.min_weight, vo = w[q].w >= a.min_weight;
+        const unsigned long long m[4] = {__builtin_amdgcn_ballot_w64(ve), __builtin_amdgcn_ballot_w64(vo),
+                                         __builtin_amdgcn_ballot_w64(w[q].x > 0.f),
+                                         __builtin_amdgcn_ballot_w64(w[q].z > 0.f)};
+        if (lane == 0) {
+            s_ve[q * 4 + wave] = m[0];
+            s_vo[q * 4 + wave] = m[1];
+            s_pe[q * 4 + wave] = m[2];
+            s_po[q * 4 + wave] = m[3];
+        }
+        some = some || ve || vo;
+    }
+    if (!__syncthreads_or(some))
+        return;
     int bx, by, bz;
     if constexpr (HASHED) {
         const int4 B = a.blocks[b];
@@ -50,82 +84,117 @@ __global__ __launch_bounds__(256) void k_sdf_extract(const SdfExtractArgs a)
         by = byz % a.nby;
         bz = byz / a.nby;
     }
-    const int tid = threadIdx.x;
-    const float2 *vox = reinterpret_cast<const float2 *>(a.vox);
-    const float2 none = make_float2(0.f, -INFINITY);
-    // the block: 4096 voxels, contiguous, two per 16-byte load
-    const float4 *blk = reinterpret_cast<const float4 *>(vox + (size_t)b * (kSdfEdge * kSdfEdge * kSdfEdge));
+    // the voxels of the neighbour blocks +x, +y, +z (null: none)
+    const float2 *nb[3];
+    if constexpr (HASHED) {
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const int f = q * 256 + tid;  // voxels 2f, 2f + 1: same row
-        const float4 w = blk[f];
-        const int x = (2 * f) & 15, y = ((2 * f) >> 4) & 15, z = (2 * f) >> 8;
-        s_v[z][y][x] = make_float2(w.x, w.y);
-        s_v[z][y][x + 1] = make_float2(w.z, w.w);
-    }
-    // first planes of the +x, +y and +z neighbour blocks
-    {
-        const int u = tid & 15, w = tid >> 4;
-        const int i0 = bx * kSdfEdge, j0 = by * kSdfEdge, k0 = bz * kSdfEdge;
-        float2 fx = none, fy = none, fz = none;
-        if constexpr (HASHED) {
-            // the neighbour's first plane: (0, u, w), (u, 0, w), (u, w, 0)
-            constexpr size_t kB = kSdfEdge * kSdfEdge * kSdfEdge;
-            const int nx = a.nbr[kNbrPerBlock * b], ny = a.nbr[kNbrPerBlock * b + 1],
-                      nz = a.nbr[kNbrPerBlock * b + 2];
-            if (nx >= 0)
-                fx = vox[(size_t)nx * kB + (size_t)((w * kSdfEdge + u) * kSdfEdge)];
-            if (ny >= 0)
-                fy = vox[(size_t)ny * kB + (size_t)(w * kSdfEdge * kSdfEdge + u)];
-            if (nz >= 0)
-                fz = vox[(size_t)nz * kB + (size_t)(w * kSdfEdge + u)];
-        } else {
-            if (bx + 1 < a.nbx)
-                fx = vox[vox_index(a.nbx, a.nby, i0 + kSdfEdge, j0 + u, k0 + w)];
-            if (by + 1 < a.nby)
-                fy = vox[vox_index(a.nbx, a.nby, i0 + u, j0 + kSdfEdge, k0 + w)];
-            if (bz + 1 < a.nbz)
-                fz = vox[vox_index(a.nbx, a.nby, i0 + u, j0 + w, k0 + kSdfEdge)];
+        for (int d = 0; d < 3; ++d) {
+            const int n = a.nbr[kNbrPerBlock * b + d];
+            nb[d] = n >= 0 ? vox + (size_t)n * kB : nullptr;
         }
-        s_v[w][u][kSdfEdge] = fx;
-        s_v[w][kSdfEdge][u] = fy;
-        s_v[kSdfEdge][w][u] = fz;
+    } else {
+        nb[0] = bx + 1 < a.nbx ? vox + (size_t)(b + 1) * kB : nullptr;
+        nb[1] = by + 1 < a.nby ? vox + ((size_t)b + a.nbx) * kB : nullptr;
+        nb[2] = bz + 1 < a.nbz ? vox + ((size_t)b + (size_t)a.nbx * a.nby) * kB : nullptr;
+    }
+    const uint32_t v = row_mask(s_ve, s_vo, tid), p = row_mask(s_pe, s_po, tid);
+    // their first planes, as far as a valid voxel of this block is beside:
+    // x of this thread's row; y and z with the thread's 16 lanes for the x of
+    // one row, even x first
+    const float2 none = make_float2(0.f, -INFINITY);
+    float2 fx = none, fy = none, fz = none;
+    {
+        const int l = tid & 15, i = (l & 7) * 2 + (l >> 3), j = tid >> 4;
+        if (nb[0] && (v & 0x8000u))
+            fx = nb[0][tid * kSdfEdge];
+        if (nb[1] && (row_mask(s_ve, s_vo, j * kSdfEdge + kSdfEdge - 1) >> l & 1u))
+            fy = nb[1][j * kSdfEdge * kSdfEdge + i];
+        if (nb[2] && (row_mask(s_ve, s_vo, (kSdfEdge - 1) * kSdfEdge + j) >> l & 1u))
+            fz = nb[2][j * kSdfEdge + i];
+    }
+    const unsigned long long fm[4] = {
+        __builtin_amdgcn_ballot_w64(fy.y >= a.min_weight), __builtin_amdgcn_ballot_w64(fz.y >= a.min_weight),
+        __builtin_amdgcn_ballot_w64(fy.x > 0.f), __builtin_amdgcn_ballot_w64(fz.x > 0.f)};
+    if (lane < 4) {
+        s_fv[0][4 * wave + lane] = (uint16_t)(fm[0] >> 16 * lane);
+        s_fv[1][4 * wave + lane] = (uint16_t)(fm[1] >> 16 * lane);
+        s_fp[0][4 * wave + lane] = (uint16_t)(fm[2] >> 16 * lane);
+        s_fp[1][4 * wave + lane] = (uint16_t)(fm[3] >> 16 * lane);
     }
     __syncthreads();
-    const int x = tid & 15, y = tid >> 4;
-    // pass 1: this thread's crossings
-    int cnt = 0;
-    for (int z = 0; z < kSdfEdge; ++z) {
-        const float2 A = s_v[z][y][x];
-        if (!(A.y >= a.min_weight))
-            continue;
-        cnt += crossing(a, A, s_v[z][y][x + 1]) ? 1 : 0;
-        cnt += crossing(a, A, s_v[z][y + 1][x]) ? 1 : 0;
-        cnt += crossing(a, A, s_v[z + 1][y][x]) ? 1 : 0;
+    const int ry = tid & 15, rz = tid >> 4;
+    uint32_t cx, cy, cz;
+    {
+        // along x: even to odd in the low byte, odd to the next even in the
+        // high one
+        const uint32_t v1 = v >> 8 | (v & 0xfeu) << 7 | (fx.y >= a.min_weight ? 0x8000u : 0u);
+        const uint32_t p1 = p >> 8 | (p & 0xfeu) << 7 | (fx.x > 0.f ? 0x8000u : 0u);
+        cx = v & v1 & (p ^ p1);
+        const uint32_t vy = ry < kSdfEdge - 1 ? row_mask(s_ve, s_vo, tid + 1) : s_fv[0][rz];
+        const uint32_t py = ry < kSdfEdge - 1 ? row_mask(s_pe, s_po, tid + 1) : s_fp[0][rz];
+        cy = v & vy & (p ^ py);
+        const uint32_t vz = rz < kSdfEdge - 1 ? row_mask(s_ve, s_vo, tid + kSdfEdge) : s_fv[1][ry];
+        const uint32_t pz = rz < kSdfEdge - 1 ? row_mask(s_pe, s_po, tid + kSdfEdge) : s_fp[1][ry];
+        cz = v & vz & (p ^ pz);
     }
-    // a block without crossings (most of the volume) ends here
-    if (!__syncthreads_or(cnt))
-        return;
+    if (!__syncthreads_or((cx | cy | cz) != 0))
+        return;  // no surface in this block
+    s_cross[tid] = cx | (unsigned long long)cy << 16 | (unsigned long long)cz << 32;
+    __syncthreads();
+    // from here thread (x, y); bit of x in a row's 16
+    const int x = tid & 15, y = tid >> 4, xb = (x >> 1) | (x & 1) << 3;
+    auto far_end = [&](int ax, int z) -> float2 {  // the edge's other voxel
+        if (ax == 0)
+            return x < kSdfEdge - 1 ? vox[(size_t)b * kB + (z * kSdfEdge + y) * kSdfEdge + x + 1]
+                                    : nb[0][(z * kSdfEdge + y) * kSdfEdge];
+        if (ax == 1)
+            return y < kSdfEdge - 1 ? vox[(size_t)b * kB + (z * kSdfEdge + y + 1) * kSdfEdge + x]
+                                    : nb[1][z * kSdfEdge * kSdfEdge + x];
+        return z < kSdfEdge - 1 ? vox[(size_t)b * kB + ((z + 1) * kSdfEdge + y) * kSdfEdge + x]
+                                : nb[2][y * kSdfEdge + x];
+    };
+    // pass 1: this thread's crossings: bit z of word ax
+    const bool gate = a.max_jump < INFINITY;
+    uint32_t mine[3] = {0u, 0u, 0u};
+#pragma unroll
+    for (int z = 0; z < kSdfEdge; ++z) {
+        const unsigned long long m = s_cross[z * kSdfEdge + y] >> xb;
+#pragma unroll
+        for (int ax = 0; ax < 3; ++ax)
+            mine[ax] |= ((uint32_t)(m >> 16 * ax) & 1u) << z;
+    }
+    if (gate) {
+        for (uint32_t any = mine[0] | mine[1] | mine[2]; any; any &= any - 1u) {
+            const int z = __builtin_ctz(any);
+            const float2 A = vox[(size_t)b * kB + (z * kSdfEdge + y) * kSdfEdge + x];
+#pragma unroll
+            for (int ax = 0; ax < 3; ++ax)
+                if (mine[ax] >> z & 1u)
+                    if (fabs((double)A.x - (double)far_end(ax, z).x) > a.max_jump)
+                        mine[ax] &= ~(1u << z);
+        }
+    }
+    const int cnt = __builtin_popcount(mine[0]) + __builtin_popcount(mine[1]) + __builtin_popcount(mine[2]);
     int total;
     const int before = block_scan256(s_wsum, cnt, total);
+    if (total == 0)
+        return;
     if (tid == 0)
         s_base = atomicAdd(a.count, (unsigned long long)total);
-    __syncthreads();
-    if (cnt == 0)
+    if (a.max_pts == 0)
         return;
+    __syncthreads();
     // pass 2: write the points
     unsigned long long n = s_base + (unsigned long long)before;
     const int i = bx * kSdfEdge + x, j = by * kSdfEdge + y;
-    for (int z = 0; z < kSdfEdge; ++z) {
-        const float2 A = s_v[z][y][x];
-        if (!(A.y >= a.min_weight))
-            continue;
-        const int k = bz * kSdfEdge + z;
+    for (uint32_t any = mine[0] | mine[1] | mine[2]; any; any &= any - 1u) {
+        const int z = __builtin_ctz(any), k = bz * kSdfEdge + z;
+        const float2 A = vox[(size_t)b * kB + (z * kSdfEdge + y) * kSdfEdge + x];
 #pragma unroll
         for (int ax = 0; ax < 3; ++ax) {
-            const float2 B = ax == 0 ? s_v[z][y][x + 1] : (ax == 1 ? s_v[z][y + 1][x] : s_v[z + 1][y][x]);
-            if (!crossing(a, A, B))
+            if (!(mine[ax] >> z & 1u))
                 continue;
+            const float2 B = far_end(ax, z);
             const double t = (double)A.x / ((double)A.x - (double)B.x);
             if (n < (unsigned long long)a.max_pts) {
                 a.pts[3 * n] = (float)(a.origin[0] + a.voxel * ((double)i + t * (ax == 0)));
@@ -150,9 +219,9 @@ hipError_t launch_sdf_extract(const SdfExtractArgs &a, bool hashed, hipStream_t 
         return e;
     if (hashed) {
         if (a.n_blocks > 0)
-            hipLaunchKernelGGL(k_sdf_extract<true>, dim3(a.n_blocks), dim3(256), 0, stream, a);
+            hipLaunchKernelGGL(k_sdf_extract<true>, dim3(xcd_grid(a.n_blocks)), dim3(256), 0, stream, a);
     } else {
-        hipLaunchKernelGGL(k_sdf_extract<false>, dim3(a.nbx * a.nby * a.nbz), dim3(256), 0, stream, a);
+        hipLaunchKernelGGL(k_sdf_extract<false>, dim3(xcd_grid(a.nbx * a.nby * a.nbz)), dim3(256), 0, stream, a);
     }
     return hipGetLastError();
 }
