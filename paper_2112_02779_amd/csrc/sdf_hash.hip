@@ -12,9 +12,9 @@
 // the block pool from a counter).  Each table entry keeps the first scan that
 // activated it (atomic minimum), so that fusion can apply a scan only to the
 // blocks that scan or an earlier one activated, as if every scan were
-// activated and then fused in turn.  Neighbouring lanes mostly produce the
-// same cube: a lane whose scan and block range equal those of the lane below
-// it leaves the inserts to that lane.
+// activated and then fused in turn.  Neighbouring returns mostly produce the
+// same cube: a return whose block range equals that of the lane below it or of
+// the row before leaves the inserts to that one.
 #include "sdf_extract.h"
 #include "sdf_hash.h"
 
@@ -74,6 +74,27 @@ __device__ __forceinline__ void bvol_insert(const BvolDev &t, int bx, int by, in
     atomicOr(t.flags, kBvolFull);
 }
 
+// Whether block (bx, by, bz) is in the table with a scan up to `frame`, by
+// cached loads, the first key and scan at once (a quarter of the blocks is
+// further on).  True is certain: during the launch a key only goes from free to
+// its value and a first scan only down, and the caches hold nothing from
+// before the launch.
+__device__ __forceinline__ bool bvol_present(const BvolDev &t, int bx, int by, int bz, int frame)
+{
+    const unsigned long long key = bvol_key(bx, by, bz);
+    uint32_t h = bvol_hash(key) & t.mask;
+    for (int probe = 0; probe < 16; ++probe) {
+        const unsigned long long k = __hip_atomic_load(t.keys + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        const int f = __hip_atomic_load(t.act + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (k == key)
+            return f <= frame;
+        if (k == kBvolEmpty)
+            return false;
+        h = (h + 1) & t.mask;
+    }
+    return false;
+}
+
 __device__ __forceinline__ int bvol_find(const BvolDev &t, int bx, int by, int bz)
 {
     if (!bvol_in_range(bx) || !bvol_in_range(by) || !bvol_in_range(bz))
@@ -91,56 +112,106 @@ __device__ __forceinline__ int bvol_find(const BvolDev &t, int bx, int by, int b
     return -1;
 }
 
+// floor(x / edge) by the reciprocal, and by the division where that could
+// round to the other side (|x / edge| < 2^20 for every block of the table, so
+// the product is within 4e-10 of the quotient).
+__device__ __forceinline__ double block_of(double x, double edge, double inv)
+{
+    const double q = x * inv, l = floor(q), f = q - l;
+    return f > 1e-9 && f < 1.0 - 1e-9 ? l : floor(x / edge);
+}
+
+// Rows of a wavefront of k_bvol_activate.
+constexpr int kActRows = 4;
+
+// Grid: (64 columns, 4 kActRows rows, scan); each wavefront takes kActRows
+// rows, one lane per column.  The cubes that are left to insert are queued in
+// shared memory, and eight lanes look up the (mostly one to eight) blocks of
+// one.  The kernel waits for its chain of dependent accesses (sensor tables,
+// ranges, table entries; VALU 32% busy), so that many short wavefronts beat
+// longer ones: 32 scans of 128 x 2048: 170 -> 56 us with 4 rows, 60 with 8, 82
+// with 16 (before: a 64-bit division per return for its place, six FP64
+// divisions, every cube inserted by one lane, through the XCDs' caches).
 __global__ __launch_bounds__(256) void k_bvol_activate(const BvolActArgs a)
 {
+    __shared__ int s_lo[4][64 * kActRows][3], s_hi[4][64 * kActRows][3];
     const int H = cload(&a.tab->H), W = cload(&a.tab->W);
     const double *row = cload(&a.tab->row), *col = cload(&a.tab->col);
-    const double r0 = cload(&a.tab->r0);
-    const int64_t hw = (int64_t)H * W, n = hw * a.n_frames;
-    const int lane = threadIdx.x & 63;
-    // whole wavefronts step together (the lane comparison below needs them)
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t base = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x & ~63); base < n; base += stride) {
-        const int64_t i = base + lane;
-        int f = 0, lo[3] = {0, 0, 0}, hi[3] = {-1, -1, -1};
-        bool on = false;
-        if (i < n) {
-            f = (int)(i / hw);
-            const int p = (int)(i - (int64_t)f * hw), v = p / W, u = p - v * W;
-            const float rf = a.ranges[i];
-            on = range_ok(rf) && !(a.clip > 0.0 && (double)rf > a.clip);
-            if (on) {
-                const V3<double> xs = unproject(row, col, r0, u, v, (double)rf);
-                const SdfFrame &F = a.f[f];
-                const double d[3] = {xs.x - F.t[0], xs.y - F.t[1], xs.z - F.t[2]};
-                for (int j = 0; j < 3; ++j) {
-                    const double x = F.R[j] * d[0] + F.R[3 + j] * d[1] + F.R[6 + j] * d[2] - a.origin[j];
-                    const double l = floor((x - a.radius) / a.edge), h = floor((x + a.radius) / a.edge);
-                    if (!(l > (double)-kBvolBias && h < (double)kBvolBias)) {
-                        on = false;  // outside the table's coordinate range
-                        break;
-                    }
-                    lo[j] = (int)l;
-                    hi[j] = (int)h;
-                }
-                if (!on)
-                    atomicOr(a.t.flags, kBvolRange);
+    const double r0 = cload(&a.tab->r0), inv = 1.0 / a.edge;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int f = blockIdx.z, frame = a.frame0 + f;
+    const SdfFrame &F = a.f[f];
+    const float *rng = a.ranges + (int64_t)f * H * W;
+    const int u = blockIdx.x * 64 + lane, v0 = ((int)blockIdx.y * 4 + wave) * kActRows;
+    double ca = 0.0, sa = 0.0;
+    if (u < W)
+        ld2(col + 2 * u, ca, sa);
+    float rf[kActRows];
+#pragma unroll
+    for (int k = 0; k < kActRows; ++k)
+        rf[k] = u < W && v0 + k < H ? rng[(int64_t)(v0 + k) * W + u] : 0.f;
+    int plo[3] = {0, 0, 0}, phi[3] = {0, 0, 0};  // the row before
+    bool pon = false;
+    int queued = 0;
+#pragma unroll
+    for (int k = 0; k < kActRows; ++k) {
+        int lo[3] = {0, 0, 0}, hi[3] = {-1, -1, -1};
+        bool on = range_ok(rf[k]) && !(a.clip > 0.0 && (double)rf[k] > a.clip);
+        if (on) {
+            const V3<double> d0 = ray_dir(sld4(row, min(v0 + k, H - 1)), ca, sa);
+            const double r = (double)rf[k];
+            const double d[3] = {r * d0.x + r0 * ca - F.t[0], r * d0.y + r0 * sa - F.t[1], r * d0.z - F.t[2]};
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                const double x = F.R[j] * d[0] + F.R[3 + j] * d[1] + F.R[6 + j] * d[2] - a.origin[j];
+                const double l = block_of(x - a.radius, a.edge, inv), h = block_of(x + a.radius, a.edge, inv);
+                // outside the table's coordinate range
+                on = on && l > (double)-kBvolBias && h < (double)kBvolBias;
+                lo[j] = (int)l;
+                hi[j] = (int)h;
+            }
+            if (!on)
+                atomicOr(a.t.flags, kBvolRange);
+        }
+        const bool above = pon && plo[0] == lo[0] && plo[1] == lo[1] && plo[2] == lo[2] && phi[0] == hi[0] &&
+                           phi[1] == hi[1] && phi[2] == hi[2];
+        const int q0 = __shfl_up(lo[0], 1), q1 = __shfl_up(lo[1], 1), q2 = __shfl_up(lo[2], 1);
+        const int p0 = __shfl_up(hi[0], 1), p1 = __shfl_up(hi[1], 1), p2 = __shfl_up(hi[2], 1);
+        const bool qon = __shfl_up(on ? 1 : 0, 1) != 0;
+        const bool left = lane > 0 && qon && q0 == lo[0] && q1 == lo[1] && q2 == lo[2] && p0 == hi[0] &&
+                          p1 == hi[1] && p2 == hi[2];
+        const bool lead = on && !left && !above;
+        const unsigned long long m = __builtin_amdgcn_ballot_w64(lead);
+        if (lead) {
+            const int at = queued + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                s_lo[wave][at][j] = lo[j];
+                s_hi[wave][at][j] = hi[j];
             }
         }
-        // the lane below with the same scan and block range inserts for both
-        const int pf = __shfl_up(f, 1), pl0 = __shfl_up(lo[0], 1), pl1 = __shfl_up(lo[1], 1),
-                  pl2 = __shfl_up(lo[2], 1), ph0 = __shfl_up(hi[0], 1), ph1 = __shfl_up(hi[1], 1),
-                  ph2 = __shfl_up(hi[2], 1);
-        const bool pon = __shfl_up(on ? 1 : 0, 1) != 0;
-        const bool same = lane > 0 && pon && pf == f && pl0 == lo[0] && pl1 == lo[1] && pl2 == lo[2] &&
-                          ph0 == hi[0] && ph1 == hi[1] && ph2 == hi[2];
-        if (!on || same)
-            continue;
-        const int frame = a.frame0 + f;
-        for (int bz = lo[2]; bz <= hi[2]; ++bz)
-            for (int by = lo[1]; by <= hi[1]; ++by)
-                for (int bx = lo[0]; bx <= hi[0]; ++bx)
-                    bvol_insert(a.t, bx, by, bz, frame);
+        queued += __builtin_popcountll(m);
+        pon = on;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            plo[j] = lo[j];
+            phi[j] = hi[j];
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    // lane bits 0..2: the block's offset in the cube (cubes of up to two
+    // blocks a side; larger ones go on in steps of two)
+    for (int e = lane >> 3; e < queued; e += 8) {
+        const int x0 = s_lo[wave][e][0], y0 = s_lo[wave][e][1], z0 = s_lo[wave][e][2];
+        const int x1 = s_hi[wave][e][0], y1 = s_hi[wave][e][1], z1 = s_hi[wave][e][2];
+        for (int z = z0 + (lane >> 2 & 1); z <= z1; z += 2)
+            for (int y = y0 + (lane >> 1 & 1); y <= y1; y += 2)
+                for (int x = x0 + (lane & 1); x <= x1; x += 2)
+                    if (!bvol_present(a.t, x, y, z, frame))
+                        bvol_insert(a.t, x, y, z, frame);
     }
 }
 
@@ -170,9 +241,9 @@ __global__ __launch_bounds__(256) void k_bvol_export(const BvolDev t, int n_bloc
 
 hipError_t launch_bvol_activate(const BvolActArgs &a, hipStream_t stream)
 {
-    const int64_t n = (int64_t)a.n_frames * a.H * a.W;
-    const int64_t blocks = std::min<int64_t>((n + 255) / 256, 8192);
-    hipLaunchKernelGGL(k_bvol_activate, dim3((unsigned)std::max<int64_t>(blocks, 1)), dim3(256), 0, stream, a);
+    const dim3 grid((unsigned)(a.W + 63) / 64u, (unsigned)(a.H + 4 * kActRows - 1) / (4u * kActRows),
+                    (unsigned)a.n_frames);
+    hipLaunchKernelGGL(k_bvol_activate, grid, dim3(256), 0, stream, a);
     return hipGetLastError();
 }
 
