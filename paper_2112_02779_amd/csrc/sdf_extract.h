@@ -25,14 +25,18 @@ struct SdfExtractArgs {
 
 constexpr int kNbrPerBlock = 7;
 
-// Workgroup w of a grid of xcd_grid(n) takes block xcd_block(w, n) (none if
-// >= n): workgroups go round robin to the 8 XCDs, so that each XCD, with a
-// cache of its own, gets a run of consecutive blocks.
-inline unsigned xcd_grid(int n) { return ((unsigned)n + 7u) / 8u * 8u; }
-__device__ __forceinline__ int xcd_block(unsigned w, int n)
+// Workgroup w of a grid of xcd_grid(n) takes block xcd_block(w) (none if >= n):
+// workgroups go round robin to the 8 XCDs, each with a cache of its own, so
+// that each XCD gets runs of kXcdRun consecutive blocks, whose common planes
+// its cache then holds.  Short runs, because the surface lies in few layers of
+// blocks: an eighth of the volume to each XCD left most of them idle (mesh of
+// 57 x 71 x 6 blocks 3708 us against 2811).
+constexpr unsigned kXcdRun = 16;
+inline unsigned xcd_grid(int n) { return ((unsigned)n + 8u * kXcdRun - 1u) / (8u * kXcdRun) * (8u * kXcdRun); }
+__device__ __forceinline__ unsigned xcd_block(unsigned w)
 {
-    const uint64_t per = ((unsigned)n + 7u) / 8u, b = (w & 7u) * per + (w >> 3);
-    return (int)(b < (uint64_t)n ? b : (uint64_t)n);
+    const unsigned k = w >> 3;
+    return (k / kXcdRun * 8u + (w & 7u)) * kXcdRun + k % kXcdRun;
 }
 
 // Exclusive prefix sum of v over a workgroup of 256 threads in thread order,

@@ -43,9 +43,9 @@ __global__ __launch_bounds__(256) void k_sdf_extract(const SdfExtractArgs a)
     __shared__ int s_wsum[4];
     __shared__ unsigned long long s_base;
     const int n_blocks = HASHED ? a.n_blocks : a.nbx * a.nby * a.nbz;
-    const int b = xcd_block(blockIdx.x, n_blocks);
-    if (b >= n_blocks)
+    if (xcd_block(blockIdx.x) >= (unsigned)n_blocks)
         return;
+    const int b = (int)xcd_block(blockIdx.x);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const float2 *vox = reinterpret_cast<const float2 *>(a.vox);
     constexpr size_t kB = kSdfEdge * kSdfEdge * kSdfEdge;

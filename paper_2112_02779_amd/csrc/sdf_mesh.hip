@@ -141,7 +141,10 @@ __global__ __launch_bounds__(256) void k_sdf_mesh(const SdfExtractArgs a)
     __shared__ int s_wsum[4];
     __shared__ uint16_t s_list[kSdfEdge * kSdfEdge * kSdfEdge];
     __shared__ unsigned long long s_base;
-    const int b = blockIdx.x;
+    const int n_blocks = HASHED ? a.n_blocks : a.nbx * a.nby * a.nbz;
+    if (xcd_block(blockIdx.x) >= (unsigned)n_blocks)
+        return;
+    const int b = (int)xcd_block(blockIdx.x);
     int bx, by, bz;
     if constexpr (HASHED) {
         const int4 B = a.blocks[b];
@@ -159,10 +162,21 @@ __global__ __launch_bounds__(256) void k_sdf_mesh(const SdfExtractArgs a)
     const float2 *vox = reinterpret_cast<const float2 *>(a.vox);
     const float2 none = make_float2(0.f, -INFINITY);
     const float4 *blk = reinterpret_cast<const float4 *>(vox + (size_t)b * kB);
+    float4 vw[8];
+    bool some = false;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        vw[q] = blk[q * 256 + tid];
+        some = some || vw[q].y >= a.min_weight || vw[q].w >= a.min_weight;
+    }
+    // every tetrahedron has its cube's first voxel, which is this block's: a
+    // block without a valid voxel ends before it asks for its neighbours
+    if (!__syncthreads_or(some))
+        return;
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
         const int f = q * 256 + tid;  // voxels 2f, 2f + 1: same row
-        const float4 w = blk[f];
+        const float4 w = vw[q];
         const int x = (2 * f) & 15, y = ((2 * f) >> 4) & 15, z = (2 * f) >> 8;
         s_v[z][y][x] = make_float2(w.x, w.y);
         s_v[z][y][x + 1] = make_float2(w.z, w.w);
@@ -278,9 +292,9 @@ hipError_t launch_sdf_mesh(const SdfExtractArgs &a, bool hashed, hipStream_t str
         return e;
     if (hashed) {
         if (a.n_blocks > 0)
-            hipLaunchKernelGGL(k_sdf_mesh<true>, dim3(a.n_blocks), dim3(256), 0, stream, a);
+            hipLaunchKernelGGL(k_sdf_mesh<true>, dim3(xcd_grid(a.n_blocks)), dim3(256), 0, stream, a);
     } else {
-        hipLaunchKernelGGL(k_sdf_mesh<false>, dim3(a.nbx * a.nby * a.nbz), dim3(256), 0, stream, a);
+        hipLaunchKernelGGL(k_sdf_mesh<false>, dim3(xcd_grid(a.nbx * a.nby * a.nbz)), dim3(256), 0, stream, a);
     }
     return hipGetLastError();
 }
