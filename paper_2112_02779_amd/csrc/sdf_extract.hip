@@ -21,24 +21,25 @@ __device__ __forceinline__ uint32_t row_mask(const unsigned long long (&even)[32
 // formed in FP64 (outside the volume: no crossing).
 //
 // Bound by reading the volume once.  So a voxel is reduced to two bits (valid,
-// positive) as it arrives, by ballots of the wavefront, and the block's masks
-// (1 KB) are all that is staged: thread (y, z) finds the crossings of its row
-// with a few operations on 16-bit words, the row's three edge directions
-// together.  The first planes of the +x, +y and +z neighbour blocks are read
-// only where a voxel beside them is valid; a block without a valid voxel ends
-// before that.  The few voxels at a crossing are read again (from a cache) for
-// the jump test and the points.  The workgroup takes one range of the output
-// with one atomic add and writes its points there in the order of thread
-// (x, y), then z, then axis (so the order of the points across blocks is not
-// defined).  Consecutive blocks go to one XCD, whose cache then holds their
-// common planes.  57 x 71 x 6 blocks (0.8 GB, 153 us at the copy rate): 250 ->
-// 175 us for a counting pass, 200 with the points (whole voxels staged in 39 KB of shared memory before).
+// positive) as it arrives, by ballots of the wavefront, and thread (y, z) finds
+// the crossings of its row with a few operations on 16-bit words, the row's
+// three edge directions together. Of the voxels only the values are staged
+// (19 KB, seven workgroups on a CU), for the jump test and the points: read
+// again from memory instead they cost small volumes 2 us a pass.  The first
+// planes of the +x, +y and +z neighbour blocks are read only where a voxel
+// beside them is valid; a block without a valid voxel ends before that.  The
+// workgroup takes one range of the output with one atomic add and writes its
+// points there in the order of thread (x, y), then z, then axis (so the order
+// of the points across blocks is not defined).  57 x 71 x 6 blocks (0.8 GB,
+// 153 us at the copy rate): 250 -> 166 us for a counting pass, 175 us with the
+// points (whole voxels staged in 39 KB of shared memory before).
 template <bool HASHED>
 __global__ __launch_bounds__(256) void k_sdf_extract(const SdfExtractArgs a)
 {
     // [q * 4 + wavefront]: 8 rows each; row z * 16 + y
     __shared__ unsigned long long s_ve[32], s_vo[32], s_pe[32], s_po[32];
     __shared__ uint16_t s_fv[2][kSdfEdge], s_fp[2][kSdfEdge];  // +y plane by z, +z plane by y
+    __shared__ float s_sdf[kSdfEdge * kSdfEdge * kSdfEdge], s_fs[3][kSdfEdge * kSdfEdge];
     __shared__ unsigned long long s_cross[kSdfEdge * kSdfEdge];  // 16 bits per axis
     __shared__ int s_wsum[4];
     __shared__ unsigned long long s_base;
@@ -68,6 +69,7 @@ __global__ __launch_bounds__(256) void k_sdf_extract(const SdfExtractArgs a)
             s_pe[q * 4 + wave] = m[2];
             s_po[q * 4 + wave] = m[3];
         }
+        *reinterpret_cast<float2 *>(s_sdf + 2 * (q * 256 + tid)) = make_float2(w[q].x, w[q].z);
         some = some || ve || vo;
     }
     if (!__syncthreads_or(some))
@@ -111,6 +113,9 @@ __global__ __launch_bounds__(256) void k_sdf_extract(const SdfExtractArgs a)
             fy = nb[1][j * kSdfEdge * kSdfEdge + i];
         if (nb[2] && (row_mask(s_ve, s_vo, (kSdfEdge - 1) * kSdfEdge + j) >> l & 1u))
             fz = nb[2][j * kSdfEdge + i];
+        s_fs[0][tid] = fx.x;
+        s_fs[1][j * kSdfEdge + i] = fy.x;
+        s_fs[2][j * kSdfEdge + i] = fz.x;
     }
     const unsigned long long fm[4] = {
         __builtin_amdgcn_ballot_w64(fy.y >= a.min_weight), __builtin_amdgcn_ballot_w64(fz.y >= a.min_weight),
@@ -143,15 +148,13 @@ __global__ __launch_bounds__(256) void k_sdf_extract(const SdfExtractArgs a)
     __syncthreads();
     // from here thread (x, y); bit of x in a row's 16
     const int x = tid & 15, y = tid >> 4, xb = (x >> 1) | (x & 1) << 3;
-    auto far_end = [&](int ax, int z) -> float2 {  // the edge's other voxel
+    auto far_end = [&](int ax, int z) -> float {  // the edge's other voxel
+        const int at = (z * kSdfEdge + y) * kSdfEdge + x;
         if (ax == 0)
-            return x < kSdfEdge - 1 ? vox[(size_t)b * kB + (z * kSdfEdge + y) * kSdfEdge + x + 1]
-                                    : nb[0][(z * kSdfEdge + y) * kSdfEdge];
+            return x < kSdfEdge - 1 ? s_sdf[at + 1] : s_fs[0][z * kSdfEdge + y];
         if (ax == 1)
-            return y < kSdfEdge - 1 ? vox[(size_t)b * kB + (z * kSdfEdge + y + 1) * kSdfEdge + x]
-                                    : nb[1][z * kSdfEdge * kSdfEdge + x];
-        return z < kSdfEdge - 1 ? vox[(size_t)b * kB + ((z + 1) * kSdfEdge + y) * kSdfEdge + x]
-                                : nb[2][y * kSdfEdge + x];
+            return y < kSdfEdge - 1 ? s_sdf[at + kSdfEdge] : s_fs[1][z * kSdfEdge + x];
+        return z < kSdfEdge - 1 ? s_sdf[at + kSdfEdge * kSdfEdge] : s_fs[2][y * kSdfEdge + x];
     };
     // pass 1: this thread's crossings: bit z of word ax
     const bool gate = a.max_jump < INFINITY;
@@ -166,11 +169,11 @@ __global__ __launch_bounds__(256) void k_sdf_extract(const SdfExtractArgs a)
     if (gate) {
         for (uint32_t any = mine[0] | mine[1] | mine[2]; any; any &= any - 1u) {
             const int z = __builtin_ctz(any);
-            const float2 A = vox[(size_t)b * kB + (z * kSdfEdge + y) * kSdfEdge + x];
+            const double A = (double)s_sdf[(z * kSdfEdge + y) * kSdfEdge + x];
 #pragma unroll
             for (int ax = 0; ax < 3; ++ax)
                 if (mine[ax] >> z & 1u)
-                    if (fabs((double)A.x - (double)far_end(ax, z).x) > a.max_jump)
+                    if (fabs(A - (double)far_end(ax, z)) > a.max_jump)
                         mine[ax] &= ~(1u << z);
         }
     }
@@ -189,13 +192,12 @@ __global__ __launch_bounds__(256) void k_sdf_extract(const SdfExtractArgs a)
     const int i = bx * kSdfEdge + x, j = by * kSdfEdge + y;
     for (uint32_t any = mine[0] | mine[1] | mine[2]; any; any &= any - 1u) {
         const int z = __builtin_ctz(any), k = bz * kSdfEdge + z;
-        const float2 A = vox[(size_t)b * kB + (z * kSdfEdge + y) * kSdfEdge + x];
+        const double A = (double)s_sdf[(z * kSdfEdge + y) * kSdfEdge + x];
 #pragma unroll
         for (int ax = 0; ax < 3; ++ax) {
             if (!(mine[ax] >> z & 1u))
                 continue;
-            const float2 B = far_end(ax, z);
-            const double t = (double)A.x / ((double)A.x - (double)B.x);
+            const double t = A / (A - (double)far_end(ax, z));
             if (n < (unsigned long long)a.max_pts) {
                 a.pts[3 * n] = (float)(a.origin[0] + a.voxel * ((double)i + t * (ax == 0)));
                 a.pts[3 * n + 1] = (float)(a.origin[1] + a.voxel * ((double)j + t * (ax == 1)));
