@@ -30,24 +30,10 @@ ROT_TOL, TRANS_TOL = 1e-4, 1e-3
 # HBM bytes per finest-level iteration counted by rocprofv3 (FETCH_SIZE,
 # WRITE_SIZE, scaled by a plain copy of known size); used only while the
 # kernel sources are the ones the counters were taken with (the bytes do not
-# depend on the launch tuning beyond the 144 B tile records).
+# depend on the launch tuning beyond the 128 B tile records).
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_icp_step_fine_odometry128x2048.json")
 SDF_COUNTS_FILE = os.path.join(ROOT, "profiles", "k_sdf_fuse_odometry100x128x2048.json")
 SDF_SOURCES = ["sdf.hip", "rir_ops.h", "rir_device.h", "rir_internal.h"]
-# VALU issue rate: 256 CUs x 4 SIMDs x 2.4 GHz, one wave64 FP32 instruction per
-# SIMD every 4 cycles (16 lanes) -> 256 * 4 * 2.4e9 / 4 wave-instructions/s
-VALU_PEAK_WAVE_INSTR = 256 * 4 * 2.4e9 / 4
-# Vector instructions one SDF evaluation (a voxel against one scan, Eq.
-# (8)-(10)) needs at least, in FP32 with the paper's projection, counted as
-# the VALU instruction counter counts them (one per wave64 instruction): the
-# rigid transform given the voxel's row terms (3 FMA); range and elevation
-# (r^2: 3, rsqrt: 1, sin(phi) = z / r: 1, field-of-view test: 2, elevation
-# bin: 2, table compare and select: 2); azimuth (rcp: 1, ratio: 1, t^2: 1,
-# degree-6 polynomial: 6 FMA, final FMA: 1, octant selects: 3); column
-# (scale and offset: 1 FMA, round: 1); signed distance and running mean
-# (r: 1, d = Omega - r: 1, truncation and clip tests: 3, weight + 1: 1, rcp:
-# 1, mean update: 2, two selects: 2): 40 in all.
-SDF_FLOOR_SLOTS = 40
 KERNEL_SOURCES = ["kernels.hip", "rir_device.h", "rir_internal.h", "rir_mlp_device.h"]
 
 
@@ -607,7 +593,7 @@ def sdf_fusion(rir, seq, oracle_sample, repeats=5):
         if k > 0:
             times.append(e0.elapsed_time(e1))
     ms = float(np.median(times))
-    masks = _sdf_cull_masks(vol, poses, trunc, r_clip, float(sm.r0), 16)
+    masks = _sdf_cull_masks(vol, poses, trunc, r_clip, float(sm.r0), 32)
     evals = sum(int(m.sum()) for m in masks) * 4096
     active = sum(int(m.any(0).sum()) for m in masks)
     img_bytes = 4.0 * sm.H * sm.W
@@ -622,16 +608,12 @@ def sdf_fusion(rir, seq, oracle_sample, repeats=5):
            "algorithmic_bytes": bytes_alg, "hbm_gbps": round(bytes_alg / (ms * 1e-3) / 1e9, 1),
            "hbm_frac": round(bytes_alg / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
            "paper_context": "40 Hz at 0.2 m voxels, 30 m clip on KITTI (hash grid, RTX 3060)"}
-    # ALU roofline against the arithmetic the method needs per evaluation (one
-    # voxel against one scan), not the kernel's own instruction count:
-    # SDF_FLOOR_SLOTS wave64 vector instructions per 64 evaluations, against
-    # the issue rate
-    wi = evals * SDF_FLOOR_SLOTS / 64.0 / (ms * 1e-3)
+    # against the bytes of every block that a scan of its launch can reach, read
+    # and written once per launch, and the scans: most of voxel_scan_evals are
+    # ruled out by layer bounds and never evaluated
     cnt = sdf_counts()
-    res["roofline"] = {"bound": "alu", "achieved": round(wi / 1e12, 4), "peak": round(VALU_PEAK_WAVE_INSTR / 1e12, 4),
-                       "unit": "T wave-instructions/s", "frac": round(wi / VALU_PEAK_WAVE_INSTR, 4),
-                       "floor_valu_per_eval": SDF_FLOOR_SLOTS,
-                       "traffic": cnt["hbm_bytes_per_sequence"] if cnt else None,
+    res["roofline"] = {"bound": "hbm", "achieved": res["hbm_gbps"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                       "frac": res["hbm_frac"], "traffic": cnt["hbm_bytes_per_sequence"] if cnt else None,
                        "counted_valu_per_eval": cnt["valu_per_eval"] if cnt else None}
     res["reconstruction"] = reconstruction_quality(rir, vol, vox, seq, r_clip, 3 * vx)
     flat = vol.to_grid(vox).reshape(-1, 2)
