@@ -61,7 +61,9 @@ constexpr int kMaxTiles = 64;
 // at most r0 and about r0 / h.  Out: the smallest range, the tangents of the
 // elevations, the azimuths.  Reciprocals and roots are the approximate ones
 // (1 ulp): the margins are far larger.  false: no bound (the layer reaches
-// the sensor's axis, or comes so near that rounding would matter).
+// the sensor's axis, or comes so near that rounding would matter).  A layer
+// whose centre lies on the axis is sent back before n is formed: n would not
+// be a number, and minima and maxima of floats skip those.
 __device__ __forceinline__ bool layer_bound(const float *fr, float z, float r0, float &rmin, float &tlo, float &thi,
                                             float &alo, float &ahi)
 {
@@ -71,7 +73,10 @@ __device__ __forceinline__ bool layer_bound(const float *fr, float z, float r0, 
                 fr[11] + x * fr[2] + y * fr[5] + z * fr[8]};
     };
     const V3<float> c = at(mid, mid);
-    const float h2 = c.x * c.x + c.y * c.y, r2 = h2 + c.z * c.z, ih = d_rsqrt(h2), ir = d_rsqrt(r2);
+    const float h2 = c.x * c.x + c.y * c.y, r2 = h2 + c.z * c.z;
+    if (!(h2 > 1e-30f))
+        return false;
+    const float ih = d_rsqrt(h2), ir = d_rsqrt(r2);
     const float nx = c.x * ih, ny = c.y * ih, mx = c.x * ir, my = c.y * ir, mz = c.z * ir;
     float along = INFINITY, qlo = INFINITY, qhi = -INFINITY, slo = INFINITY, shi = -INFINITY;
     rmin = INFINITY;
@@ -89,7 +94,7 @@ __device__ __forceinline__ bool layer_bound(const float *fr, float z, float r0, 
     }
     rmin -= r0;
     const float ext = e * (fabsf(fr[0]) + fabsf(fr[1]) + fabsf(fr[2]) + fabsf(fr[3]) + fabsf(fr[4]) + fabsf(fr[5]));
-    // also false for a NaN (the centre on the axis)
+    // (an overflow leaves an infinite or NaN bound: also false)
     if (!(along > 8.0f * r0 + 0.02f * (r2 * ir + ext)))
         return false;
     const float smax = fmaxf(fabsf(slo), fabsf(shi)), cmin = d_rsqrt(1.0f + smax * smax);
