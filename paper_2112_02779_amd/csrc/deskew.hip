@@ -143,15 +143,15 @@ __global__ __launch_bounds__(256, R0 ? 4 : 5) void k_deskew(const SensorTab<doub
     for (int k = 0; k < 3; ++k)
         t[k] = s_pose[9 + k][c];
     uint32_t old[N], bits[N];  // of the previous chunk's swaps
-    int at[N];
+    uint32_t *at[N];
 #pragma unroll
     for (int j = 0; j < N; ++j)
-        old[j] = bits[j] = 0u, at[j] = 0;
+        old[j] = bits[j] = 0u, at[j] = dst;
     auto settle = [&]() {
 #pragma unroll
         for (int j = 0; j < N; ++j)
             if (old[j] > bits[j])  // taken (not 0) by a farther return
-                atomicMin(dst + at[j], bits[j]);
+                atomicMin(at[j], bits[j]);
     };
     for (int v0 = vb + wave * N; v0 < ve; v0 += kDeskewWaves * N) {
         float rf[N];
@@ -177,10 +177,10 @@ __global__ __launch_bounds__(256, R0 ? 4 : 5) void k_deskew(const SensorTab<doub
 #pragma unroll
         for (int j = 0; j < N; ++j) {
             bits[j] = __float_as_uint((float)r2[j]);
-            at[j] = v2[j] * W + u2[j];
+            at[j] = dst + ((size_t)v2[j] * W + u2[j]);
             old[j] = 0u;
             if (ok[j] && bits[j] < kInfBits)
-                old[j] = atomicCAS(dst + at[j], 0u, bits[j]);
+                old[j] = atomicCAS(at[j], 0u, bits[j]);
         }
     }
     settle();
