@@ -2204,8 +2204,12 @@ extern "C" rir_status rir_mlp_train_step(rir_mlp *m, const float *feats, const f
         if (m->gpart)
             HIP_TRY(hipFree(m->gpart));
         m->gpart = nullptr;
-        HIP_TRY(hipMalloc(reinterpret_cast<void **>(&m->gpart), (size_t)nb * kMlpGradRecord * sizeof(float)));
-        m->gpart_blocks = nb;
+        m->gpart_blocks = 0;
+        // for smaller batches too, so that one that follows needs no memory
+        // (a training loop's last batch; a stream under capture)
+        const int cap = mlp_grad_blocks_upto(B);
+        HIP_TRY(hipMalloc(reinterpret_cast<void **>(&m->gpart), (size_t)cap * kMlpGradRecord * sizeof(float)));
+        m->gpart_blocks = cap;
     }
     HIP_TRY(launch_mlp_grad(m->dev(), feats, labels, B, m->gpart, nb, st));
     m->step += 1;

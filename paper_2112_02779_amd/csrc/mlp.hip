@@ -386,6 +386,15 @@ int mlp_grad_blocks(int64_t B)
     return (int)(nb < 1 ? 1 : (nb > 512 ? 512 : nb)) * kMlpGradWaves;
 }
 
+// Each step of mlp_grad_per halves the records, so the most lie at B or at the
+// last batch of a step before it.
+int mlp_grad_blocks_upto(int64_t B)
+{
+    const int64_t a = B < 512 * 16 ? B : 512 * 16, b = B < 512 * 32 ? B : 512 * 32;
+    const int na = mlp_grad_blocks(a), nb = mlp_grad_blocks(b), n = mlp_grad_blocks(B);
+    return na > nb ? (na > n ? na : n) : (nb > n ? nb : n);
+}
+
 hipError_t launch_mlp_forward(const MlpDev &m, const float *feats, int64_t B, float *w_out, hipStream_t stream)
 {
     int64_t nb = (B + 255) / 256;

@@ -172,7 +172,10 @@ hipError_t launch_mlp_grad(const MlpDev &m, const float *feats, const float *lab
 hipError_t launch_mlp_adam(const float *gpart, int nblocks, int64_t B, float lr, int step, float *master,
                            float *bias, float *m1, float *m2, uint16_t *wbf, float *loss_out, float *grads_out,
                            hipStream_t stream);
+// Gradient records of a batch of B samples, and the most that any batch of up
+// to B samples has.
 int mlp_grad_blocks(int64_t B);
+int mlp_grad_blocks_upto(int64_t B);
 constexpr int kMlpGradRecord = 5185 + 1;  // gradient + loss per block
 // Allocation-free training step: its gradient records live in a fixed device
 // array of kMlpScratchRecords records per GPU, which holds the records of
