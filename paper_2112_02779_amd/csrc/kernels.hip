@@ -668,7 +668,7 @@ __device__ __forceinline__ void step_segments(const StepArgs &a, const MlpInfer 
             const T J1 = xz[j] * n0 - xx[j] * n2;
             const T J2 = xx[j] * n1 - xy[j] * n0;
             const T tq = e * inv_delta;
-            const T wh = d_rsqrt((T)1 + tq * tq);
+            const T wh = d_rsqrt_inf((T)1 + tq * tq);
             T w = wh;
             const int i = in[j] ? vs[j] * Wl + us[j] : -1;
             if constexpr (kRec) {

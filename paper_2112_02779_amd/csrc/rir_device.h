@@ -199,6 +199,15 @@ __device__ __forceinline__ double d_rsqrt(double x)
     const double h = fma(-x * y, y, 1.0);
     return fma(y * h, fma(0.375, h, 0.5), y);
 }
+// The same, 0 for infinity (FP64: the maximum drops the NaN of inf * 0): the
+// pseudo-Huber weight of a residual whose square by kernel sizes overflows.
+__device__ __forceinline__ float d_rsqrt_inf(float x) { return d_rsqrt(x); }
+__device__ __forceinline__ double d_rsqrt_inf(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    const double h = fmax(fma(-x * y, y, 1.0), -1.0);
+    return fma(y * h, fma(0.375, h, 0.5), y);
+}
 __device__ __forceinline__ float d_sqrt(float x) { return sqrt(x); }
 __device__ __forceinline__ double d_sqrt(double x) { return x * d_rsqrt(x); }  // x > 0 normal
 __device__ __forceinline__ float d_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
