@@ -181,9 +181,10 @@ __device__ __forceinline__ bool pca_tile(const SensorTab<double> &S, const float
     // |r - rc| <= edge_rel rc: the FP32 difference is within 2^-24 of the true
     // one, so it decides outside a band of 4e-7 around the limit; a wavefront
     // with a window point in that band (one in thousands) sums again by the
-    // FP64 test
+    // FP64 test.  (Less one subnormal step, which a limit among the subnormal
+    // floats could be rounded up by; rounding keeps the order for the upper end)
     const double rcd = (double)rc, lim = edge_rel * rcd;
-    const float sure = (float)(lim * (1.0 - 4e-7)), never = (float)(lim * (1.0 + 4e-7));
+    const float sure = (float)fma(lim, 1.0 - 4e-7, -0x1p-149), never = (float)(lim * (1.0 + 4e-7));
     const double pcx = s_x[ci], pcy = s_y[ci], pcz = s_z[ci];
     // r d = p - r0 (cos a, sin a, 0)
     double ca = 0.0, sa = 0.0;
