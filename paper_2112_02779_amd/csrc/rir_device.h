@@ -426,14 +426,33 @@ __device__ __forceinline__ int beam_at(const LevelView<T> &V, T t, T z)
     return elev_row(eb0, cload(&S->bin_lo[0]), cload(&S->bin_scale[0]), (T)(nb0 - 1), z * d_rsqrt(t * t + z * z),
                     dummy);
 }
+// Row v in that search, with the distance t along its ray and its offset's
+// cosine and sine.
 template <typename T>
-__device__ __forceinline__ int next_beam(const LevelView<T> &V, T x, T y, T z, int v)
+struct Beam {
+    int v;
+    T t, cth, sth;
+};
+template <typename T>
+__device__ __forceinline__ Beam<T> beam_of(const LevelView<T> &V, T x, T y, int v)
 {
     const T r0 = V.r0, rho2 = x * x + y * y;
     const T rho2c = rho2 > (T)4 * r0 * r0 ? rho2 : (T)4 * r0 * r0;
     const V4<T> rw = bld4<T>(V.row, (uint32_t)v * (uint32_t)(4 * sizeof(T)));
-    const T t = d_sqrt(rho2c - r0 * r0 * rw.w * rw.w) - r0 * rw.z;
-    return beam_at(V, t, z);
+    return {v, d_sqrt(rho2c - r0 * r0 * rw.w * rw.w) - r0 * rw.z, rw.z, rw.w};
+}
+template <typename T>
+__device__ __forceinline__ int next_beam(const LevelView<T> &V, T x, T y, T z, int v)
+{
+    return beam_at(V, beam_of(V, x, y, v).t, z);
+}
+// Where the search starts: a beam without an offset.
+template <typename T>
+__device__ __forceinline__ int first_beam(const LevelView<T> &V, T x, T y, T z)
+{
+    const T r0 = V.r0, rho2 = x * x + y * y;
+    const T rho2c = rho2 > (T)4 * r0 * r0 ? rho2 : (T)4 * r0 * r0;
+    return beam_at(V, d_sqrt(rho2c - r0 * r0), z);
 }
 // The row after two steps of that search; true if the second step still moved
 // (one more, the last, then settles it).  Straight-line, so that a caller
@@ -441,10 +460,7 @@ __device__ __forceinline__ int next_beam(const LevelView<T> &V, T x, T y, T z, i
 template <typename T>
 __device__ __forceinline__ bool beam_row(const LevelView<T> &V, T x, T y, T z, int &v)
 {
-    const T r0 = V.r0, rho2 = x * x + y * y;
-    const T rho2c = rho2 > (T)4 * r0 * r0 ? rho2 : (T)4 * r0 * r0;
-    const int v0 = beam_at(V, d_sqrt(rho2c - r0 * r0), z);
-    const int v1 = next_beam(V, x, y, z, v0);
+    const int v1 = next_beam(V, x, y, z, first_beam(V, x, y, z));
     v = next_beam(V, x, y, z, v1);
     return v != v1;
 }
@@ -467,7 +483,8 @@ __device__ __forceinline__ bool beam_row(const LevelView<T> &V, T x, T y, T z, i
 // receiver-offset branch out (callers that know r0 = 0); POW2 = true wraps
 // the column with a mask (callers that know Wl is a power of two).
 template <typename T, bool R0, bool POW2>
-__device__ __forceinline__ bool project_beam(const LevelView<T> &V, T x, T y, T z, int v0, int &ul, int &vl, T &r)
+__device__ __forceinline__ bool project_beam(const LevelView<T> &V, T x, T y, T z, const Beam<T> &B, int &ul, int &vl,
+                                             T &r)
 {
     T r2, th;
     bool ok = true;
@@ -476,14 +493,10 @@ __device__ __forceinline__ bool project_beam(const LevelView<T> &V, T x, T y, T 
         const rsrc_t thr = make_rsrc(cload(&S->theta), (uint32_t)(cload(&S->H) * sizeof(T)));
         const T r0 = V.r0, rho2 = x * x + y * y, z2 = z * z;
         ok = rho2 > (T)4 * r0 * r0;
-        const T rho2c = ok ? rho2 : (T)4 * r0 * r0;
-        const V4<T> rw = bld4<T>(V.row, (uint32_t)v0 * (uint32_t)(4 * sizeof(T)));
-        const T cth = rw.z, sth = rw.w;
-        const T t = d_sqrt(rho2c - r0 * r0 * sth * sth) - r0 * cth;
-        r2 = t * t + z2;
-        const T ys = t * sth, xs = r0 + t * cth;
+        r2 = B.t * B.t + z2;
+        const T ys = B.t * B.sth, xs = r0 + B.t * B.cth;
         const T off = ys < (T)0 ? -atan2_abs(ys, xs) : atan2_abs(ys, xs);
-        th = azimuth(y, x) - off + bld1<T>(thr, (uint32_t)v0 * (uint32_t)sizeof(T));
+        th = azimuth(y, x) - off + bld1<T>(thr, (uint32_t)B.v * (uint32_t)sizeof(T));
         th = th < (T)0 ? th + two_pi<T>() : th;
         th = th < (T)0 ? th + two_pi<T>() : th;
         th = th >= two_pi<T>() ? th - two_pi<T>() : th;
@@ -539,27 +552,35 @@ __device__ __forceinline__ void project_n(const LevelView<T> &V, const T (&x)[N]
             }
 #pragma unroll
             for (int j = 0; j < N; ++j)
-                ok[j] = project_beam<T, true, POW2>(V, x[j], y[j], z[j], vb[j], ul[j], vl[j], r[j]) & ok[j];
+                ok[j] = project_beam<T, true, POW2>(V, x[j], y[j], z[j], beam_of(V, x[j], y[j], vb[j]), ul[j], vl[j],
+                                                    r[j]) & ok[j];
             return;
         }
     }
 #pragma unroll
     for (int j = 0; j < N; ++j)
-        ok[j] = project_beam<T, false, POW2>(V, x[j], y[j], z[j], 0, ul[j], vl[j], r[j]) & ok[j];
+        ok[j] = project_beam<T, false, POW2>(V, x[j], y[j], z[j], Beam<T>{}, ul[j], vl[j], r[j]) & ok[j];
 }
 
+// One point: the search ends where the row stays, and its last row is the
+// result's (a second step, which project_n always takes, is seldom needed: 2^20
+// points of a staggered 64 x 1000 sensor 12.4 us with it, 10.3 without).
 template <typename T, bool R0 = true, bool POW2 = false>
 __device__ __forceinline__ bool project(const LevelView<T> &V, T x, T y, T z, int &ul, int &vl, T &r)
 {
     if constexpr (R0) {
         if (V.r0 > (T)0) {
-            int v;
-            if (beam_row(V, x, y, z, v))
-                v = next_beam(V, x, y, z, v);
-            return project_beam<T, true, POW2>(V, x, y, z, v, ul, vl, r);
+            Beam<T> B = beam_of(V, x, y, first_beam(V, x, y, z));
+            for (int k = 0; k < 3; ++k) {
+                const int v = beam_at(V, B.t, z);
+                if (v == B.v)
+                    break;
+                B = beam_of(V, x, y, v);
+            }
+            return project_beam<T, true, POW2>(V, x, y, z, B, ul, vl, r);
         }
     }
-    return project_beam<T, false, POW2>(V, x, y, z, 0, ul, vl, r);
+    return project_beam<T, false, POW2>(V, x, y, z, Beam<T>{}, ul, vl, r);
 }
 
 // ----------------------------------------------------------------------------- normals
