@@ -49,6 +49,16 @@ constexpr int kSdfXcdRun = 8;
 // else coarse ones; one that spans more (a layer next to the sensor) is
 // evaluated unseen.
 constexpr int kMaxTiles = 64;
+// Without tile maxima (few block-scans, a stream under capture, no free slot)
+// launches of up to kFewFrames scans, or into up to kFewBlocks blocks, or of a
+// sensor with a receiver offset take a column's voxels four at a time for each
+// scan instead of a layer's scans four at a time: a layer after the other is a
+// chain of 16 projections and gathers, which only many scans and blocks hide.
+// 64 x 1024 scans, us a call, layers against columns: 1 scan into 16 x 16 x 4
+// blocks 17.8 and 12.2, 12 scans 76.9 and 73.8; into 40 x 40 x 6 blocks 3 scans
+// 139 and 118, 4 scans 150 and 150, 12 scans 393 and 410; 64 x 1000 with an
+// offset, 12 scans into 40 x 40 x 6 blocks 1397 and 1359.
+constexpr int kFewFrames = 3, kFewBlocks = 2048;
 
 // Bounds of layer z (voxels (0..15, 0..15, z)) of a block in one scan, from
 // the block's constants fr (s_fr).  The layer's four corners go through the
@@ -174,6 +184,40 @@ __device__ __forceinline__ bool layer_seen(const SdfArgs &a, const LevelView<flo
     return top >= nb;
 }
 
+// Voxel (x, y, z) of the block in scan f (s_fr constants s_f): its range r there
+// and the return om of the pixel it projects to; false: it does not project.
+template <bool R0, bool POW2>
+__device__ __forceinline__ bool sample(const SdfArgs &a, const LevelView<float> &V, rsrc_t img, const float *s_f,
+                                       int f, float x, float y, float z, float &om, float &r)
+{
+    const float4 *fr = reinterpret_cast<const float4 *>(s_f);
+    const float4 q0 = fr[0], q1 = fr[1], q2 = fr[2];
+    // tb + x c0 + y c1, then + z c2
+    const float px = fmaf(y, q0.w, fmaf(x, q0.x, q2.y));
+    const float py = fmaf(y, q1.x, fmaf(x, q0.y, q2.z));
+    const float pz = fmaf(y, q1.y, fmaf(x, q0.z, q2.w));
+    const float xs = fmaf(z, q1.z, px), ys = fmaf(z, q1.w, py), zs = fmaf(z, q2.x, pz);
+    const uint32_t H = (uint32_t)V.Hl, W = (uint32_t)V.Wl;
+    int u, v;
+    const bool ok = project<float, R0, POW2>(V, xs, ys, zs, u, v, r);
+    // u, v are in range even when ok is false: the gather is unconditional
+    om = __uint_as_float(bld_u32s(img, ((uint32_t)v * W + (uint32_t)u) * 4u, (uint32_t)f * H * W * 4u));
+    return ok;
+}
+
+// Eq. (9)-(10) for one voxel and one scan.
+__device__ __forceinline__ void update(const SdfArgs &a, bool ok, float om, float r, float &sd, float &wt, bool &chg)
+{
+    float d = om - r;
+    const bool use = ok && range_ok(om) && om <= a.clip && d >= -a.trunc;
+    d = fminf(d, a.trunc);
+    const float wn = wt + 1.0f;
+    const float sn = fmaf(d - sd, d_rcp(wn), sd);
+    sd = use ? sn : sd;
+    wt = use ? wn : wt;
+    chg = chg || use;
+}
+
 }  // namespace
 
 // Tile maxima of n_frames scans: the bit pattern of the largest return of at
@@ -216,7 +260,8 @@ __global__ __launch_bounds__(256) void k_range_tiles(const float *ranges, int n_
         tiles[(size_t)n_frames * H * nt + (size_t)fr * ntc + c] = all;
 }
 
-template <bool R0, bool POW2, bool HASHED>
+// FEW: see kFewFrames.
+template <bool R0, bool POW2, bool HASHED, bool FEW>
 __global__ __launch_bounds__(256) void k_sdf_fuse(const SdfArgs a)
 {
     __shared__ __align__(16) float s_fr[kSdfFrames][kFrameWords];
@@ -303,6 +348,39 @@ __global__ __launch_bounds__(256) void k_sdf_fuse(const SdfArgs a)
     const int H = V.Hl, W = V.Wl;
     const rsrc_t img = make_rsrc(a.ranges, (uint32_t)a.n_frames * (uint32_t)H * (uint32_t)W * 4u);
     const int lane = tid & 63;
+    const float x = (float)(tid & (kSdfEdge - 1)), y = (float)(tid >> 4);
+    float2 *vb = reinterpret_cast<float2 *>(a.vox) + (size_t)b * (kSdfEdge * kSdfEdge * kSdfEdge) + tid;
+
+    if constexpr (FEW) {
+        constexpr int kVox = 4, kStep = kSdfEdge / kVox;
+        for (int z0 = 0; z0 < kStep; ++z0) {
+            float sd[kVox], wt[kVox];
+            bool chg[kVox];
+#pragma unroll
+            for (int k = 0; k < kVox; ++k) {
+                const float2 st = vb[(z0 + k * kStep) * kSdfEdge * kSdfEdge];
+                sd[k] = st.x;
+                wt[k] = st.y;
+                chg[k] = false;
+            }
+            for (uint32_t m = reach; m != 0; m &= m - 1) {
+                const int f = __builtin_ctz(m);
+                float om[kVox], r[kVox];
+                bool ok[kVox];
+#pragma unroll
+                for (int k = 0; k < kVox; ++k)
+                    ok[k] = sample<R0, POW2>(a, V, img, s_fr[f], f, x, y, (float)(z0 + k * kStep), om[k], r[k]);
+#pragma unroll
+                for (int k = 0; k < kVox; ++k)
+                    update(a, ok[k], om[k], r[k], sd[k], wt[k], chg[k]);
+            }
+#pragma unroll
+            for (int k = 0; k < kVox; ++k)
+                if (chg[k])
+                    vb[(z0 + k * kStep) * kSdfEdge * kSdfEdge] = make_float2(sd[k], wt[k]);
+        }
+        return;
+    }
 
     // ---- which layers each scan can update: a wavefront takes four scans at
     // a time, 16 lanes (layers) each
@@ -321,8 +399,6 @@ __global__ __launch_bounds__(256) void k_sdf_fuse(const SdfArgs a)
 
     // ---- evaluation, layer by layer; the next layer's state is on its way
     // while this one's scans are fused
-    const float x = (float)(tid & (kSdfEdge - 1)), y = (float)(tid >> 4);
-    float2 *vb = reinterpret_cast<float2 *>(a.vox) + (size_t)b * (kSdfEdge * kSdfEdge * kSdfEdge) + tid;
     int z = __builtin_ctz(layers);
     float2 next = vb[z * kSdfEdge * kSdfEdge];
     while (layers != 0) {
@@ -392,15 +468,15 @@ hipError_t launch_range_tiles(const float *ranges, int n_frames, int H, int W, f
     return hipGetLastError();
 }
 
-template <bool HASHED>
+template <bool HASHED, bool FEW>
 static void launch_sdf_fuse_h(const SdfArgs &a, bool r0, bool pow2, int nblk, hipStream_t stream)
 {
     if (r0)
-        hipLaunchKernelGGL((k_sdf_fuse<true, false, HASHED>), dim3(nblk), dim3(256), 0, stream, a);
+        hipLaunchKernelGGL((k_sdf_fuse<true, false, HASHED, FEW>), dim3(nblk), dim3(256), 0, stream, a);
     else if (pow2)
-        hipLaunchKernelGGL((k_sdf_fuse<false, true, HASHED>), dim3(nblk), dim3(256), 0, stream, a);
+        hipLaunchKernelGGL((k_sdf_fuse<false, true, HASHED, FEW>), dim3(nblk), dim3(256), 0, stream, a);
     else
-        hipLaunchKernelGGL((k_sdf_fuse<false, false, HASHED>), dim3(nblk), dim3(256), 0, stream, a);
+        hipLaunchKernelGGL((k_sdf_fuse<false, false, HASHED, FEW>), dim3(nblk), dim3(256), 0, stream, a);
 }
 
 hipError_t launch_sdf_fuse(const SdfArgs &a, bool r0, bool pow2, bool hashed, hipStream_t stream)
@@ -409,10 +485,18 @@ hipError_t launch_sdf_fuse(const SdfArgs &a, bool r0, bool pow2, bool hashed, hi
     if (n <= 0)
         return hipSuccess;
     const int nblk = a.xcd_remap ? (n + run - 1) / run * run : n;
-    if (hashed)
-        launch_sdf_fuse_h<true>(a, r0, pow2, nblk, stream);
-    else
-        launch_sdf_fuse_h<false>(a, r0, pow2, nblk, stream);
+    const bool few = !a.tiles && (r0 || a.n_frames <= kFewFrames || n <= kFewBlocks);
+    if (hashed) {
+        if (few)
+            launch_sdf_fuse_h<true, true>(a, r0, pow2, nblk, stream);
+        else
+            launch_sdf_fuse_h<true, false>(a, r0, pow2, nblk, stream);
+    } else {
+        if (few)
+            launch_sdf_fuse_h<false, true>(a, r0, pow2, nblk, stream);
+        else
+            launch_sdf_fuse_h<false, false>(a, r0, pow2, nblk, stream);
+    }
     return hipGetLastError();
 }
 
