@@ -121,20 +121,18 @@ __device__ __forceinline__ double block_of(double x, double edge, double inv)
     return f > 1e-9 && f < 1.0 - 1e-9 ? l : floor(x / edge);
 }
 
-// Rows of a wavefront of k_bvol_activate.
-constexpr int kActRows = 4;
-
-// Grid: (64 columns, 4 kActRows rows, scan); each wavefront takes kActRows
-// rows, one lane per column.  The cubes that are left to insert are queued in
+// Grid: (64 columns, 4 ROWS rows, scan); each wavefront takes ROWS rows, one
+// lane per column.  The cubes that are left to insert are queued in
 // shared memory, and eight lanes look up the (mostly one to eight) blocks of
 // one.  The kernel waits for its chain of dependent accesses (sensor tables,
 // ranges, table entries; VALU 32% busy), so that many short wavefronts beat
 // longer ones: 32 scans of 128 x 2048: 170 -> 56 us with 4 rows, 60 with 8, 82
 // with 16 (before: a 64-bit division per return for its place, six FP64
 // divisions, every cube inserted by one lane, through the XCDs' caches).
+template <int ROWS>
 __global__ __launch_bounds__(256) void k_bvol_activate(const BvolActArgs a)
 {
-    __shared__ int s_lo[4][64 * kActRows][3], s_hi[4][64 * kActRows][3];
+    __shared__ int s_lo[4][64 * ROWS][3], s_hi[4][64 * ROWS][3];
     const int H = cload(&a.tab->H), W = cload(&a.tab->W);
     const double *row = cload(&a.tab->row), *col = cload(&a.tab->col);
     const double r0 = cload(&a.tab->r0), inv = 1.0 / a.edge;
@@ -142,19 +140,19 @@ __global__ __launch_bounds__(256) void k_bvol_activate(const BvolActArgs a)
     const int f = blockIdx.z, frame = a.frame0 + f;
     const SdfFrame &F = a.f[f];
     const float *rng = a.ranges + (int64_t)f * H * W;
-    const int u = blockIdx.x * 64 + lane, v0 = ((int)blockIdx.y * 4 + wave) * kActRows;
+    const int u = blockIdx.x * 64 + lane, v0 = ((int)blockIdx.y * 4 + wave) * ROWS;
     double ca = 0.0, sa = 0.0;
     if (u < W)
         ld2(col + 2 * u, ca, sa);
-    float rf[kActRows];
+    float rf[ROWS];
 #pragma unroll
-    for (int k = 0; k < kActRows; ++k)
+    for (int k = 0; k < ROWS; ++k)
         rf[k] = u < W && v0 + k < H ? rng[(int64_t)(v0 + k) * W + u] : 0.f;
     int plo[3] = {0, 0, 0}, phi[3] = {0, 0, 0};  // the row before
     bool pon = false;
     int queued = 0;
 #pragma unroll
-    for (int k = 0; k < kActRows; ++k) {
+    for (int k = 0; k < ROWS; ++k) {
         int lo[3] = {0, 0, 0}, hi[3] = {-1, -1, -1};
         bool on = range_ok(rf[k]) && !(a.clip > 0.0 && (double)rf[k] > a.clip);
         if (on) {
@@ -241,9 +239,18 @@ __global__ __launch_bounds__(256) void k_bvol_export(const BvolDev t, int n_bloc
 
 hipError_t launch_bvol_activate(const BvolActArgs &a, hipStream_t stream)
 {
-    const dim3 grid((unsigned)(a.W + 63) / 64u, (unsigned)(a.H + 4 * kActRows - 1) / (4u * kActRows),
-                    (unsigned)a.n_frames);
-    hipLaunchKernelGGL(k_bvol_activate, grid, dim3(256), 0, stream, a);
+    // fewer rows a wavefront where the launch would not give each of the 256
+    // CUs four workgroups: the inserts of a wavefront's cubes are its chain
+    // (one scan of 16 x 256 into an empty table 36.2 us with 4 rows, 18.9 with
+    // 1; a call with one scan of 128 x 2048 127 and 122)
+    const unsigned nc = (unsigned)(a.W + 63) / 64u, nf = (unsigned)a.n_frames;
+    auto rows = [&](unsigned r) { return ((unsigned)a.H + 4u * r - 1u) / (4u * r); };
+    if ((int64_t)nc * rows(4) * nf >= 1024)
+        hipLaunchKernelGGL(k_bvol_activate<4>, dim3(nc, rows(4), nf), dim3(256), 0, stream, a);
+    else if ((int64_t)nc * rows(2) * nf >= 1024)
+        hipLaunchKernelGGL(k_bvol_activate<2>, dim3(nc, rows(2), nf), dim3(256), 0, stream, a);
+    else
+        hipLaunchKernelGGL(k_bvol_activate<1>, dim3(nc, rows(1), nf), dim3(256), 0, stream, a);
     return hipGetLastError();
 }
 
