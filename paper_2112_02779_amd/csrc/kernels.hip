@@ -767,8 +767,17 @@ __device__ __forceinline__ void solve_from_tiles(const StepArgs &a, int pair, in
 // FINE tags the finest-level instance (same code) so that profiles report it
 // separately.  FUSED instances (one tile per workgroup) also solve: the
 // workgroup that finishes a pair's last tile applies that pair's update.
+// Waves per SIMD the compiler keeps room for.  The lean instances without the
+// solve (solve_in_step 0) need 91, 73 and 62 registers; left alone it takes up
+// to 119 for values that it moves out of the tile loop, one or two waves fewer
+// (32 pairs of 128x2048: 884 -> 858 us, chunks of 2 884 -> 861, of 1 1060 -> 969).
+template <typename T, int WMODE, int CHUNK, bool LEAN, bool FUSED>
+constexpr int step_waves()
+{
+    return sizeof(T) == 4 && WMODE == 0 && LEAN && !FUSED ? (CHUNK == 4 ? 5 : (CHUNK == 2 ? 6 : 7)) : 1;
+}
 template <typename T, int WMODE, bool FINE, int CHUNK, bool LEAN, bool FUSED>
-__global__ __launch_bounds__(256) void k_icp_step(StepArgs a)
+__global__ __launch_bounds__(256, (step_waves<T, WMODE, CHUNK, LEAN, FUSED>())) void k_icp_step(StepArgs a)
 {
     __shared__ T s_wave[4][kAccum];
     __shared__ int s_last;
