@@ -550,9 +550,10 @@ constexpr bool kLanesEnabled = false;
 
 static rir_status check_tuning(const rir_tuning *t)
 {
-    if (!(t->block == 64 || t->block == 128 || t->block == 256))
+    static_assert(kMaxBlock == 256 && kMaxPxPerThread == 16, "the messages below");
+    if (!(t->block == 64 || t->block == 128 || t->block == kMaxBlock))
         return fail(RIR_E_INVALID, "rir_tuning.block must be 64, 128 or 256");
-    if (t->px_per_thread < 1 || t->px_per_thread > 16)
+    if (t->px_per_thread < 1 || t->px_per_thread > kMaxPxPerThread)
         return fail(RIR_E_INVALID, "rir_tuning.px_per_thread must be in 1..16");
     if (t->grid_mult < 0 || t->grid_mult > 64)
         return fail(RIR_E_INVALID, "rir_tuning.grid_mult must be in 0..64");

@@ -63,7 +63,9 @@ constexpr int kFlagStride = kMaxLevels + 1;
 // Concurrent sub-batches (streams) of the coarse levels of one batch.
 constexpr int kMaxLanes = 4;
 constexpr int kAccum = 32;  // record entries per tile
-constexpr int kTileMaxPx = 256 * 16;  // pixels of the largest tile a tuning gives
+// The largest block and px_per_thread of a tuning, and the pixels of the tile
+// they give.
+constexpr int kMaxBlock = 256, kMaxPxPerThread = 16, kTileMaxPx = kMaxBlock * kMaxPxPerThread;
 
 enum StepMode { kStepNormal = 0, kStepFallback = 1, kStepDebug = 2 };
 
