@@ -1668,9 +1668,9 @@ static TileSlot *tile_slot(const rir_sensor *s, int32_t per, hipStream_t st)
     for (auto &q : s->tile_slots)
         if (!t && hipEventQuery(q.done) == hipSuccess)
             t = &q;
-    (void)hipGetLastError();  // "not ready" of a query
     if (t && hipStreamWaitEvent(st, t->done, 0) != hipSuccess)
         t = nullptr;
+    (void)hipGetLastError();  // "not ready" of a query, a wait that failed
     if (!t && s->tile_slots.size() < kTileSlots) {
         TileSlot q;
         void *mem = nullptr;
