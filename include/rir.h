@@ -361,8 +361,11 @@ typedef struct {
  * FP32 per-voxel arithmetic; the per-block sensor-frame offsets are formed in
  * FP64.  Work is enqueued on `stream` in launches of up to 32 scans; a block
  * that no scan of a launch can reach (farther than r_clip + trunc + r0 from
- * every sensor, with both limits set) is not touched.  n_frames = 0 is a
- * no-op.  Errors: RIR_E_INVALID (null, n_frames < 0, non-finite pose,
+ * every sensor, with both limits set) is not touched.  The first calls that
+ * find no free table of tile maxima allocate one with the sensor (a word per
+ * 16 pixels and one per 256, of 32 scans: 2.2 MB for 128 x 2048; up to four a
+ * sensor, released with it); under graph capture, or when all four are in use by other streams, a call does
+ * without and gives the same volume.  n_frames = 0 is a no-op.  Errors: RIR_E_INVALID (null, n_frames < 0, non-finite pose,
  * origin, trunc or r_clip, voxel <= 0), RIR_E_SHAPE (block count < 1 or
  * above 2^31 - 1, 16 scans of H x W at or above 2 GiB), RIR_E_HIP. */
 rir_status rir_sdf_integrate(const rir_sensor *sensor, const rir_volume_desc *vol, float *voxels, int32_t n_frames,

@@ -98,7 +98,7 @@ constexpr int kDeskewCols = 64, kDeskewWaves = 4, kDeskewChunk = 2, kDeskewRows 
 // in by compare-and-swap, any other by an atomic minimum; the swap's answer
 // is looked at one chunk later.  100 scans of 128 x 2048: 258 -> 138 us with
 // the fill, 4 rows at a time 150 (fewer wavefronts); the floor of reading and
-// writing once is 40 us, the FP64 instructions (VALU 61% busy) take 70.
+// writing once is 40 us, the FP64 instructions (VALU 66% busy) take 79.
 template <bool R0, bool POW2>
 __global__ __launch_bounds__(256, R0 ? 4 : 5) void k_deskew(const SensorTab<double> *tab, const float *in,
                                                             uint32_t *out, int rows, Twists tw)

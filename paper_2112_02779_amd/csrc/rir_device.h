@@ -473,7 +473,7 @@ __device__ __forceinline__ bool beam_row(const LevelView<T> &V, T x, T y, T z, i
 // (rho = |p_xy|) and the ray azimuth is atan2(p_y, p_x) - atan2(t sin th_v,
 // r0 + t cos th_v) + th_v; only the beam index is iterated (it changes only
 // near an elevation midpoint; three steps at most), and project_beam takes
-// the result v0.  Points within 2 r0 of the axis do not
+// the beam found.  Points within 2 r0 of the axis do not
 // project.  Then the range, the elevation row by the inverse table and the
 // column from the azimuth minus the row's offset, rounded half up and wrapped
 // (Sec. 4.1: continuous geometry at the finest level, nearest strided row and

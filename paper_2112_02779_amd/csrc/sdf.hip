@@ -2,9 +2,10 @@
 // grid of 16^3-voxel blocks on gfx950.
 //
 // One workgroup of 256 threads owns one block; thread (x, y) takes the 16
-// voxels (x, y, 0..15) of its column layer by layer, reading each voxel's
-// state once and writing it once per launch whatever the number of scans
-// fused into it (up to kSdfFrames).  Per scan and voxel: the sensor-frame
+// voxels (x, y, 0..15) of its column layer by layer (four at a time in small
+// launches, see kFewFrames), reading each voxel's state once and writing it
+// once per launch whatever the number of scans fused into it (up to
+// kSdfFrames).  Per scan and voxel: the sensor-frame
 // position R x + t (three FMAs from per-block constants built in FP64), the
 // projection of Eq. (3)-(4) at the finest level, one gather of the scan's
 // range, the signed distance of Eq. (9) and the running mean of Eq. (10).  A
@@ -13,9 +14,9 @@
 // neither is a z-layer that no pixel of the scan can update (below); a layer
 // no scan of the launch can update is neither read nor written.
 //
-// Which layers a scan can update.  The kernel is bound by VALU issue, and of
-// the evaluations within the clip distance only about 5% change a voxel: most
-// voxels lie behind the surface their pixel sees, project to a pixel without
+// Which layers a scan can update.  Evaluating every voxel for every scan within
+// reach the kernel was bound by VALU issue (97% busy), and of those evaluations
+// only about 5% change a voxel: most voxels lie behind the surface their pixel sees, project to a pixel without
 // a return or fall outside the field of view.  So before any evaluation each
 // lane bounds, for one layer of the block and one scan, the pixel rectangle
 // the layer projects to and the smallest range of its voxels, looks up the
@@ -29,8 +30,10 @@
 // height and about 8% in a layer that holds one that does.  Measured on that
 // sequence: 4.85 ms without, 2.0 ms with rectangles read pixel by pixel for
 // four slabs a block, 1.53 ms with an early exit and 32 scans a launch
-// instead of 16, 1.07 ms with tile maxima for 16 layers (398 -> 97 million
-// vector instructions per 16 -> 32 scans).
+// instead of 16, 1.07 ms with tile maxima for 16 layers (399 million vector
+// instructions a launch of 16 scans before, 104 million a launch of 32 now).
+// Now the vector units are 58% busy over a launch; the rest waits for the
+// layer tests' look-ups, a chain each, and for the gathers.
 #include <type_traits>
 
 #include "rir_ops.h"
